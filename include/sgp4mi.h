@@ -329,8 +329,8 @@ void sgp4_plan_destroy(sgp4_plan* plan);
  * (FP64) or float (FP32_MIXED), gv nullable (zero).  Points with codes 1, 2,
  * 3, 4, 7 contribute nothing.  Deep-space satellites are not differentiated:
  * their gelem columns are NaN.  gelem: device float64 [7][n].  FP32 is rejected
- * (SGP4_E_PRECISION).  One 256-lane workgroup per satellite: n < 2^24 (else
- * SGP4_E_SIZE). */
+ * (SGP4_E_PRECISION).  At most one 256-lane workgroup per satellite: n < 2^24
+ * (else SGP4_E_SIZE). */
 int sgp4_vjp(int64_t n, const double* elem, const void* consts, const double* t, int64_t T, int precision,
              const void* gr, const void* gv, double* gelem, void* stream);
 
@@ -356,10 +356,10 @@ int sgp4_vjp_ragged(int64_t n, const double* elem, const void* consts, const int
  * with s = (r_x, r_y, r_z, v_x, v_y, v_z) (km, km/s) and theta as for sgp4_vjp.
  * jac: device float64 [6][7][n*T], written in full; NaN where the point's
  * code is 1, 2, 3, 4 or 7 and at every point of a deep-space satellite (not
- * differentiated).  elem, consts, t as for sgp4_vjp.  Computed in forward
- * mode: the seven element tangents carried through one pass of the
- * propagation (in two groups of four and three directions), each point's
- * columns stored as they come.  FP32 is rejected (SGP4_E_PRECISION).
+ * differentiated).  elem, consts, t as for sgp4_vjp.  FP64: the state's
+ * derivatives with respect to the point's mean orbit, contracted with each
+ * element's tangent of it; mixed: the seven element tangents carried through
+ * the propagation.  FP32 is rejected (SGP4_E_PRECISION).
  * n < 2^24 as for sgp4_vjp. */
 int sgp4_jacobian(int64_t n, const double* elem, const void* consts, const double* t, int64_t T, int precision,
                   double* jac, void* stream);

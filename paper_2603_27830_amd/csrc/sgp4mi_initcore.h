@@ -71,13 +71,17 @@ using dual::value;
 // propagation kernels (any argument, no quadrant logic, no library branches).
 __device__ __forceinline__ void sin_cos(double x, double* s, double* c) { sincos_rr(x, s, c); }
 using dual::sin_cos;
-// Quotient: for double, the reciprocal estimate refined by Newton steps times
-// the numerator (within about an ulp of the rounded quotient, and a shorter
-// dependency chain than the correctly rounded division); for dual numbers, their
-// own division.
+// Quotient: the reciprocal estimate refined by Newton steps times the
+// numerator (within about an ulp of the rounded quotient, and a shorter
+// dependency chain than the correctly rounded division); for dual numbers the
+// same, one reciprocal for the value and the derivative.
 __device__ __forceinline__ double quot(double a, double b) { return a * rcp(b); }
 template <class A, class B>
-__device__ __forceinline__ Dual1 quot(A a, B b) { return Dual1(a) / Dual1(b); }
+__device__ __forceinline__ Dual1 quot(A a, B b) {
+  const Dual1 x(a), y(b);
+  const double r = rcp(y.v), q = x.v * r;
+  return Dual1(q, (x.d - q * y.d) * r);
+}
 
 struct GravIn {
   double radius, j2, j4, ke, j3oj2;

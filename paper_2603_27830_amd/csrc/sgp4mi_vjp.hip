@@ -2,26 +2,72 @@
 // differentiated elements (paper section 5: gradients of the state with
 // respect to the initial orbital elements, including B*).
 //
-// One workgroup per satellite.  Each lane recomputes the forward pass of its
-// points (nothing from the forward launch is stored), then runs the reverse
-// sweep of the per-point steps by hand, giving the adjoint of every
-// per-satellite constant in double.  Kepler's equation is differentiated
-// through the implicit-function theorem at its root.  Each lane accumulates
-// the adjoints of its points; the workgroup then sums them in a fixed order
-// (wavefront butterfly, then the wavefronts in index order: no atomics, so
-// results repeat bit for bit), and seven lanes push the sums through the
-// initialisation by forward-mode duals, one element each:
-// g_m = sum_k cbar_k * d c_k / d theta_m.
+// A workgroup of four wavefronts takes a group of 1 to 8 consecutive
+// satellites.  The group's points are cut into chunks of 64 points of one
+// satellite, dealt to the wavefronts in turn; a lane recomputes the forward
+// pass of its points (nothing from the forward launch is stored) and sweeps
+// the per-point steps in reverse by hand, accumulating the adjoints of the
+// per-satellite constants in double.  Kepler's equation is differentiated
+// through the implicit-function theorem at its root.  A wavefront sums its
+// lanes' adjoints per satellite in a fixed order, the group adds its
+// wavefronts' sums in index order (no atomics, so results repeat bit for bit),
+// and seven lanes per satellite push the sums through the initialisation by
+// forward-mode duals, one element each: g_m = sum_k cbar_k * d c_k / d theta_m.
+#include "sgp4mi_grad64.h"
 #include "sgp4mi_initcore.h"
-#include "sgp4mi_point.h"
+
+#include <algorithm>
 
 namespace sgp4mi {
 
 constexpr int kVjpBlock = 256;
-// Workgroups per compute unit the register allocation must allow: two (two
-// wavefronts per SIMD) in FP64, whose reverse sweep otherwise spills past 256
-// registers and runs one wavefront per SIMD; three in the mixed path.
-template <class TP> constexpr int kVjpBlocksPerCU = sizeof(TP) == 8 ? 2 : 3;
+constexpr int kVjpWaves = kVjpBlock / 64;
+// Satellites per group at most: 7 x 8 lanes of one wavefront run the VJP's
+// duals; the Jacobian keeps 2,240 bytes of sensitivities per satellite.
+constexpr int kGroupMax = 8, kJacGroupMax = 4;
+// Workgroups per compute unit the register allocation must allow (one
+// wavefront per SIMD each).
+template <class TP> constexpr int kVjpBlocksPerCU = 3;
+template <class TP> constexpr int kJacBlocksPerCU = sizeof(TP) == 8 ? 2 : 3;
+
+// Satellites per group, so that a group has about `want` 64-point chunks.  The
+// duals of the initialisation (a serial chain of ~1,000 instructions on seven
+// lanes per satellite) are paid once per group, and with several groups on a
+// compute unit the chunks of one cover the duals of another.  Larger groups,
+// or groups on batches of fewer than 1,024 satellites, only leave compute units
+// without work.  VJP, 9,341 satellites: 1,000 times in groups of one 376 us, of
+// two 348; lists of 79 points on average 166 us in one workgroup each, 153 in
+// groups of eight (with the rest of an orbit fit, about 100 us, in both).
+// Jacobian, 9,341 x 500: groups of two 468 us, of four 498.  The rule looks at
+// n and the mean list length alone, so a dense grid given as lists is grouped
+// as the grid is.
+static int group_size(int64_t n, int64_t points, int want) {
+  const int64_t chunks = std::max<int64_t>(1, (points / n + 63) / 64);
+  return int(std::max<int64_t>(1, std::min<int64_t>({kGroupMax, want / chunks, n / 1024})));
+}
+
+// Sum of each of acc[0..K) over the wavefront's 64 lanes: lane l ends with the
+// sums of (l / 8) (K / 8) + k, k < K / 8, in acc[k].  The lanes exchange halves
+// three times (a lane keeps half of its values and hands its partner the other
+// half), so 24 values take 30 exchanges instead of the 144 of one butterfly
+// per value; the order of the additions is the butterfly's.
+template <int K>
+__device__ __forceinline__ void wave_sum(double* acc, int lane) {
+  static_assert(K % 8 == 0, "three halvings");
+#pragma unroll
+  for (int level = 0; level < 3; ++level) {
+    const int half = K >> (level + 1), off = 32 >> level;
+    const bool upper = (lane & off) != 0;
+#pragma unroll
+    for (int k = 0; k < half; ++k) {
+      const double keep = upper ? acc[half + k] : acc[k], give = upper ? acc[k] : acc[half + k];
+      acc[k] = keep + __shfl_xor(give, off, 64);
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < K / 8; ++k)
+    for (int off = 4; off > 0; off >>= 1) acc[k] += __shfl_xor(acc[k], off, 64);
+}
 
 template <class TS, class TP>
 __device__ __forceinline__ uint32_t point_vjp(const SatC<TS, TP>& c, const Grav& g, double t_abs, const TP gr[3],
@@ -306,6 +352,139 @@ __device__ __forceinline__ uint32_t point_vjp(const SatC<TS, TP>& c, const Grav&
   return mrt < TP(1) ? 6u : 0u;
 }
 
+// Satellite i's list: its first point and its length.  Ragged offsets are
+// clamped to [0, nnz] (and the end to at least the start), so malformed ones
+// never reach outside t, the cotangents or the output.
+template <bool kRagged>
+__device__ __forceinline__ void list_of(const int64_t* __restrict__ offsets, int64_t i, int64_t T, int64_t P,
+                                        int64_t* p0, int64_t* cnt) {
+  if (kRagged) {
+    int64_t lo = offsets[i], hi = offsets[i + 1];
+    lo = lo < 0 ? 0 : (lo > P ? P : lo);
+    hi = hi < lo ? lo : (hi > P ? P : hi);
+    *p0 = lo;
+    *cnt = hi - lo;
+  } else {
+    *p0 = i * T;
+    *cnt = T;
+  }
+}
+
+// ------------------------------------------------------------------ FP64 --
+// Dense: times t[0..T) of every satellite, P = n T; CSR: satellite i's points
+// offsets[i] .. offsets[i+1]-1 at times t[p], P = nnz.  Cotangent rows of P.
+//
+// Bound by VALU issue (FP64, about 710 instructions per 64 points, 61% of the
+// launch's cycles) and by the latencies that three wavefronts per SIMD leave
+// open.  9,341 x 1,000 with both cotangents 523 -> 347 us; 9,341 lists of 79
+// points on average 316 -> 85 us (one 256-lane workgroup per list before).
+template <bool kRagged>
+__global__ void __launch_bounds__(kVjpBlock, kVjpBlocksPerCU<double>)
+    vjp64_kernel(RecordView rv, int64_t n, const double* __restrict__ elem, const int64_t* __restrict__ offsets,
+                 const double* __restrict__ t, int64_t T, int64_t P, const double* __restrict__ gr,
+                 const double* __restrict__ gv, double* __restrict__ gelem, int group) {
+  static_assert(kGroupMax == 8, "a group's sums are kept by the eight lanes that share them");
+  __shared__ double consts[kGroupMax][kNGrad64];
+  __shared__ uint32_t infos[kGroupMax];
+  // the lanes' sums of the satellite at hand, then the wavefronts' of the group
+  __shared__ double sums[kVjpWaves][kNAdj64][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t sat0 = int64_t(blockIdx.x) * group;
+  const int ns = int(n - sat0 < group ? n - sat0 : group);
+  if (int(threadIdx.x) < ns) infos[threadIdx.x] = rv.slots[sat0 + threadIdx.x].info;
+  for (int q = threadIdx.x; q < ns * kNRec; q += kVjpBlock)
+    consts[q / kNRec][q % kNRec] = rv.slots[sat0 + q / kNRec].d[q % kNRec];
+  __syncthreads();
+  if (int(threadIdx.x) < ns) grad64_extras(consts[threadIdx.x], rv.hdr[kHJ3oJ2]);
+  __syncthreads();
+  const Grav g = load_grav(rv);
+  uint32_t dealt = 0;  // chunks of the satellites before this one
+  double kept[kNAdj64 / 8];
+#pragma unroll
+  for (int k = 0; k < kNAdj64 / 8; ++k) kept[k] = 0.0;
+  for (int s = 0; s < ns; ++s) {
+    int64_t p0, cnt;
+    list_of<kRagged>(offsets, sat0 + s, T, P, &p0, &cnt);
+    const uint32_t info = __builtin_amdgcn_readfirstlane(infos[s]);
+    // a satellite without states or derivatives (codes at epoch, deep space) has no work
+    const int64_t chunks = (info & (kInfoCodeMask | kInfoDeep)) ? 0 : (cnt + 63) / 64;
+    const int64_t c0 = (uint32_t(wave) - dealt) & (kVjpWaves - 1);
+    dealt += uint32_t(chunks);
+    const Adj64Sums lane_sums{&sums[wave][0][lane]};
+    lane_sums.clear();
+    const double* tt = kRagged ? t + p0 : t;
+    for (int64_t j = chunks ? c0 * 64 + lane : cnt; j < cnt; j += kVjpBlock) {
+      const int64_t q = p0 + j;
+      const double grp[3] = {gr[q], gr[P + q], gr[2 * P + q]};
+      double gvp[3] = {0.0, 0.0, 0.0};
+      if (gv) {
+        gvp[0] = gv[q];
+        gvp[1] = gv[P + q];
+        gvp[2] = gv[2 * P + q];
+      }
+      // constants are read from LDS where a step uses them: the fences keep
+      // the compiler from holding them all in registers over the loop
+      asm volatile("" ::: "memory");
+      Point64 pt;
+      double U;
+      uint32_t code = point64_secular(consts[s], tt[j], pt, &U);
+      if (code == 0) code = point64_orbit(consts[s], g, pt.t, U, pt);
+      if (code == 0 || code == 6) point64_reverse(consts[s], g, pt, grp, gvp, lane_sums);
+    }
+    if (c0 < chunks) {
+      double acc[kNAdj64];
+#pragma unroll
+      for (int k = 0; k < kNAdj64; ++k) acc[k] = lane_sums.col[64 * k];
+      wave_sum<kNAdj64>(acc, lane);
+      if ((lane & 7) == s) {
+#pragma unroll
+        for (int k = 0; k < kNAdj64 / 8; ++k) kept[k] = acc[k];
+      }
+    }
+  }
+  __syncthreads();
+  if ((lane & 7) < ns) {
+#pragma unroll
+    for (int k = 0; k < kNAdj64 / 8; ++k) sums[wave][(lane >> 3) * (kNAdj64 / 8) + k][lane & 7] = kept[k];
+  }
+  __syncthreads();
+  const int s = int(threadIdx.x) / 7, m = int(threadIdx.x) - 7 * s;
+  if (s < ns) {
+    const int64_t i = sat0 + s;
+    const uint32_t info = infos[s];
+    // deep-space satellites are not differentiated: NaN
+    double out = (info & kInfoDeep) ? __builtin_nan("") : 0.0;
+    if ((info & (kInfoCodeMask | kInfoDeep)) == 0) {
+      Dual1 el[7];
+      for (int k = 0; k < 7; ++k) el[k] = Dual1(elem[k * n + i], k == m ? 1.0 : 0.0);
+      GravIn gi{rv.hdr[kHRadius], rv.hdr[kHJ2], rv.hdr[kHJ4], rv.hdr[kHKe], rv.hdr[kHJ3oJ2]};
+      Dual1 rec[kNRec];
+      uint32_t code;
+      bool isimp, dsp;
+      init_record<Dual1>(gi, el, rec, &code, &isimp, &dsp);
+      auto cbar = [&](int k) {
+        double x = sums[0][k][s];
+        for (int w = 1; w < kVjpWaves; ++w) x += sums[w][k][s];
+        return x;
+      };
+#pragma unroll
+      for (int q = 0; q < kAInc; ++q) {
+        const double cb = cbar(q);
+        if (cb != 0.0) out += cb * rec[kAdjRec[q]].d;
+      }
+      const double cs = consts[s][kBC5] * cbar(kAE0);
+      if (cs != 0.0) out += cs * rec[kSinM0].d;
+      if (m == 2) out += cbar(kAInc);
+    }
+    gelem[m * n + i] = out;
+  }
+}
+
+// ----------------------------------------------------------------- mixed --
+// The mixed path keeps one workgroup per satellite and the textbook order of
+// the reverse sweep: its sums leave in double, but they are sums of float
+// terms, and another grouping or order moves single points by a float rounding
+// (groups measured 250 us against 294 at 9,341 x 1,000).
 // One workgroup's satellite i: its points p0 + j for j < cnt, at times tt[j],
 // with cotangent rows of P entries (dense: p0 = i T, tt = t; CSR: p0 =
 // offsets[i], tt = t + p0).
@@ -397,6 +576,10 @@ __global__ void __launch_bounds__(kVjpBlock, kVjpBlocksPerCU<TP>)
 // jac[(c * 7 + m) * P + p] = d state_c / d theta_m at point p, c over r_x, r_y,
 // r_z, v_x, v_y, v_z and m over the seven differentiated elements; NaN where
 // the point's code is 1, 2, 4 or 7.
+//
+// FP64: jacobian64_kernel, the point's derivative columns (sgp4mi_grad64.h)
+// contracted with the elements' tangents.  Mixed: jacobian_kernel, forward mode
+// carried through every step, whose float rounding its results keep.
 //
 // Forward mode: one workgroup per satellite; seven lanes first push the unit
 // tangents of the elements through the initialisation (forward-mode duals)
@@ -801,8 +984,101 @@ __device__ __forceinline__ void jac_sat(const RecordView& rv, int64_t n, const d
   }
 }
 
+// FP64: the VJP's groups, chunks and forward pass; then the point's columns
+// and, per element, the tangent of the secular terms contracted with them (the
+// duals run before the points, since the points need the sensitivities).  The
+// stores are ordinary ones: rows of T doubles start inside cache lines, and the
+// L2 merges the pieces (non-temporal 468 us, ordinary 404 at 9,341 x 500).
+// 9,341 x 500: 566 -> 410 us; 9,341 x 30: 138 -> 59 us.  VALU issue takes 46%
+// of the launch, the 1.57 GB of stores need about 240 us; two wavefronts per
+// SIMD (the columns hold 72 registers) leave latencies open in between.
+template <bool kRagged>
+__global__ void __launch_bounds__(kVjpBlock, kJacBlocksPerCU<double>)
+    jacobian64_kernel(RecordView rv, int64_t n, const double* __restrict__ elem, const int64_t* __restrict__ offsets,
+                      const double* __restrict__ t, int64_t T, int64_t P, double* __restrict__ jac, int group) {
+  __shared__ double consts[kJacGroupMax][kNGrad64];
+  __shared__ double sens[kJacGroupMax][7][kNRec];  // d c_k / d theta_m
+  __shared__ double parked[kVjpWaves][kNParked64][64];
+  __shared__ uint32_t infos[kGroupMax];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t sat0 = int64_t(blockIdx.x) * group;
+  const int ns = int(n - sat0 < group ? n - sat0 : group);
+  if (int(threadIdx.x) < ns) infos[threadIdx.x] = rv.slots[sat0 + threadIdx.x].info;
+  for (int q = threadIdx.x; q < ns * kNRec; q += kVjpBlock)
+    consts[q / kNRec][q % kNRec] = rv.slots[sat0 + q / kNRec].d[q % kNRec];
+  {
+    const int s = int(threadIdx.x) / 7, m = int(threadIdx.x) - 7 * s;
+    if (s < ns && (rv.slots[sat0 + s].info & (kInfoCodeMask | kInfoDeep)) == 0) {
+      Dual1 el[7];
+      for (int k = 0; k < 7; ++k) el[k] = Dual1(elem[k * n + sat0 + s], k == m ? 1.0 : 0.0);
+      GravIn gi{rv.hdr[kHRadius], rv.hdr[kHJ2], rv.hdr[kHJ4], rv.hdr[kHKe], rv.hdr[kHJ3oJ2]};
+      Dual1 rec[kNRec];
+      uint32_t code;
+      bool isimp, dsp;
+      init_record<Dual1>(gi, el, rec, &code, &isimp, &dsp);
+#pragma unroll
+      for (int k = 0; k < kNRec; ++k) sens[s][m][k] = k == kEpochMin ? 0.0 : rec[k].d;
+    }
+  }
+  __syncthreads();
+  if (int(threadIdx.x) < ns) grad64_extras(consts[threadIdx.x], rv.hdr[kHJ3oJ2]);
+  __syncthreads();
+  const Grav g = load_grav(rv);
+  const double qnan = __builtin_nan("");
+  uint32_t dealt = 0;  // chunks of the satellites before this one
+  for (int s = 0; s < ns; ++s) {
+    int64_t p0, cnt;
+    list_of<kRagged>(offsets, sat0 + s, T, P, &p0, &cnt);
+    const uint32_t info = __builtin_amdgcn_readfirstlane(infos[s]);
+    const bool bad = (info & (kInfoCodeMask | kInfoDeep)) != 0;
+    const int64_t c0 = (uint32_t(wave) - dealt) & (kVjpWaves - 1);
+    dealt += uint32_t((cnt + 63) / 64);
+    const double* tt = kRagged ? t + p0 : t;
+    for (int64_t j = c0 * 64 + lane; j < cnt; j += kVjpBlock) {
+      typedef __attribute__((address_space(1))) double* GDouble;
+      double* out = jac + p0 + j;
+      int64_t row = 7 * P;
+      asm volatile("" : "+s"(row));
+      Point64 pt;
+      bool ok = false;
+      if (!bad) {
+        asm volatile("" ::: "memory");
+        double U;
+        uint32_t code = point64_secular(consts[s], tt[j], pt, &U);
+        if (code == 0) {
+          park(&parked[wave][0][lane], pt);
+          asm volatile("" ::: "memory");
+          code = point64_orbit(consts[s], g, pt.t, U, pt);
+        }
+        ok = code == 0 || code == 6;
+      }
+      if (ok) {
+        Columns64 col;
+        point64_columns(consts[s], g, pt, col);
+        unpark(&parked[wave][0][lane], pt);
+#pragma unroll
+        for (int m = 0; m < 7; ++m) {
+          double d[6];
+          element_tangent(m, sens[s][m], consts[s], pt, col, d);
+          // the next row's address follows from the last one's (forty-two
+          // multiples of P kept over the loop overflow the scalar registers)
+          GDouble to = (GDouble)(out + m * P);
+#pragma unroll
+          for (int q = 0; q < 6; ++q) {
+            *to = d[q];
+            to += row;
+            asm volatile("" : "+v"(to));
+          }
+        }
+      } else {
+        for (int q = 0; q < 42; ++q, out += P) *out = qnan;
+      }
+    }
+  }
+}
+
 template <class TS, class TP>
-__global__ void __launch_bounds__(kVjpBlock, kVjpBlocksPerCU<TP>)
+__global__ void __launch_bounds__(kVjpBlock, kJacBlocksPerCU<TP>)
     jacobian_kernel(RecordView rv, int64_t n, const double* __restrict__ elem, const double* __restrict__ t,
                     int64_t T, double* __restrict__ jac) {
   const int64_t i = blockIdx.x;
@@ -811,7 +1087,7 @@ __global__ void __launch_bounds__(kVjpBlock, kVjpBlocksPerCU<TP>)
 
 // CSR time lists, offsets clamped per workgroup as for the ragged VJP.
 template <class TS, class TP>
-__global__ void __launch_bounds__(kVjpBlock, kVjpBlocksPerCU<TP>)
+__global__ void __launch_bounds__(kVjpBlock, kJacBlocksPerCU<TP>)
     jacobian_ragged_kernel(RecordView rv, int64_t n, const double* __restrict__ elem,
                            const int64_t* __restrict__ offsets, const double* __restrict__ t, int64_t nnz,
                            double* __restrict__ jac) {
@@ -822,47 +1098,43 @@ __global__ void __launch_bounds__(kVjpBlock, kVjpBlocksPerCU<TP>)
   jac_sat<TS, TP>(rv, n, elem, i, lo, hi - lo, nnz, t + lo, jac);
 }
 
+template <bool kRagged>
+static hipError_t jacobian64_go(int64_t n, const double* elem, const RecordView& rv, const int64_t* offsets,
+                                const double* t, int64_t T, int64_t P, double* jac, hipStream_t s) {
+  const int group = std::min(kJacGroupMax, group_size(n, P, 16));
+  hipLaunchKernelGGL(jacobian64_kernel<kRagged>, dim3(unsigned((n + group - 1) / group)), dim3(kVjpBlock), 0, s, rv, n,
+                     elem, offsets, t, T, P, jac, group);
+  return hipGetLastError();
+}
+
 hipError_t launch_jacobian(int precision, int64_t n, const double* elem, const void* consts, const double* t,
                            int64_t T, double* jac, hipStream_t s) {
   const RecordView rv = view_of(consts, n);
-  if (precision == 0)
-    hipLaunchKernelGGL((jacobian_kernel<double, double>), dim3(unsigned(n)), dim3(kVjpBlock), 0, s, rv, n, elem, t, T,
-                       jac);
-  else if (precision == 2)
-    hipLaunchKernelGGL((jacobian_kernel<double, float>), dim3(unsigned(n)), dim3(kVjpBlock), 0, s, rv, n, elem, t, T,
-                       jac);
-  else
-    return hipErrorInvalidValue;
+  if (precision == 0) return jacobian64_go<false>(n, elem, rv, nullptr, t, T, n * T, jac, s);
+  if (precision != 2) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((jacobian_kernel<double, float>), dim3(unsigned(n)), dim3(kVjpBlock), 0, s, rv, n, elem, t, T,
+                     jac);
+  return hipGetLastError();
+}
+
+template <bool kRagged>
+static hipError_t vjp64_go(int64_t n, const double* elem, const RecordView& rv, const int64_t* offsets,
+                           const double* t, int64_t T, int64_t P, const void* gr, const void* gv, double* gelem,
+                           hipStream_t s) {
+  const int group = group_size(n, P, 32);
+  hipLaunchKernelGGL(vjp64_kernel<kRagged>, dim3(unsigned((n + group - 1) / group)), dim3(kVjpBlock), 0, s, rv, n,
+                     elem, offsets, t, T, P, static_cast<const double*>(gr), static_cast<const double*>(gv), gelem,
+                     group);
   return hipGetLastError();
 }
 
 hipError_t launch_vjp(int precision, int64_t n, const double* elem, const void* consts, const double* t, int64_t T,
                       const void* gr, const void* gv, double* gelem, hipStream_t s) {
   const RecordView rv = view_of(consts, n);
-  if (precision == 0) {
-    hipLaunchKernelGGL((vjp_kernel<double, double>), dim3(unsigned(n)), dim3(kVjpBlock), 0, s, rv, n, elem, t, T,
-                       static_cast<const double*>(gr), static_cast<const double*>(gv), gelem);
-  } else if (precision == 2) {
-    hipLaunchKernelGGL((vjp_kernel<double, float>), dim3(unsigned(n)), dim3(kVjpBlock), 0, s, rv, n, elem, t, T,
-                       static_cast<const float*>(gr), static_cast<const float*>(gv), gelem);
-  } else {
-    return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
-hipError_t launch_jacobian_ragged(int precision, int64_t n, const double* elem, const void* consts,
-                                  const int64_t* offsets, const double* t, int64_t nnz, double* jac, hipStream_t s) {
-  const RecordView rv = view_of(consts, n);
-  if (precision == 0) {
-    hipLaunchKernelGGL((jacobian_ragged_kernel<double, double>), dim3(unsigned(n)), dim3(kVjpBlock), 0, s, rv, n,
-                       elem, offsets, t, nnz, jac);
-  } else if (precision == 2) {
-    hipLaunchKernelGGL((jacobian_ragged_kernel<double, float>), dim3(unsigned(n)), dim3(kVjpBlock), 0, s, rv, n,
-                       elem, offsets, t, nnz, jac);
-  } else {
-    return hipErrorInvalidValue;
-  }
+  if (precision == 0) return vjp64_go<false>(n, elem, rv, nullptr, t, T, n * T, gr, gv, gelem, s);
+  if (precision != 2) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((vjp_kernel<double, float>), dim3(unsigned(n)), dim3(kVjpBlock), 0, s, rv, n, elem, t, T,
+                     static_cast<const float*>(gr), static_cast<const float*>(gv), gelem);
   return hipGetLastError();
 }
 
@@ -870,15 +1142,20 @@ hipError_t launch_vjp_ragged(int precision, int64_t n, const double* elem, const
                              const double* t, int64_t nnz, const void* gr, const void* gv, double* gelem,
                              hipStream_t s) {
   const RecordView rv = view_of(consts, n);
-  if (precision == 0) {
-    hipLaunchKernelGGL((vjp_ragged_kernel<double, double>), dim3(unsigned(n)), dim3(kVjpBlock), 0, s, rv, n, elem,
-                       offsets, t, nnz, static_cast<const double*>(gr), static_cast<const double*>(gv), gelem);
-  } else if (precision == 2) {
-    hipLaunchKernelGGL((vjp_ragged_kernel<double, float>), dim3(unsigned(n)), dim3(kVjpBlock), 0, s, rv, n, elem,
-                       offsets, t, nnz, static_cast<const float*>(gr), static_cast<const float*>(gv), gelem);
-  } else {
-    return hipErrorInvalidValue;
-  }
+  if (precision == 0) return vjp64_go<true>(n, elem, rv, offsets, t, 0, nnz, gr, gv, gelem, s);
+  if (precision != 2) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((vjp_ragged_kernel<double, float>), dim3(unsigned(n)), dim3(kVjpBlock), 0, s, rv, n, elem,
+                     offsets, t, nnz, static_cast<const float*>(gr), static_cast<const float*>(gv), gelem);
+  return hipGetLastError();
+}
+
+hipError_t launch_jacobian_ragged(int precision, int64_t n, const double* elem, const void* consts,
+                                  const int64_t* offsets, const double* t, int64_t nnz, double* jac, hipStream_t s) {
+  const RecordView rv = view_of(consts, n);
+  if (precision == 0) return jacobian64_go<true>(n, elem, rv, offsets, t, 0, nnz, jac, s);
+  if (precision != 2) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((jacobian_ragged_kernel<double, float>), dim3(unsigned(n)), dim3(kVjpBlock), 0, s, rv, n, elem,
+                     offsets, t, nnz, jac);
   return hipGetLastError();
 }
 
