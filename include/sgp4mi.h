@@ -180,14 +180,16 @@ int sgp4_propagate_elements_ex(const double* grav, const double* ref_jd, int64_t
  *   count: device int64, set to the number of events found (which may exceed
  *      capacity: only the first `capacity` found are written).
  *   ws: device scratch of at least sgp4_screen_workspace_bytes(n, T) bytes
- *      (about 12 n T + 4 T n / 4: sorted float x, y and satellite index per
- *      point and bucket offsets per time), else SGP4_E_WORKSPACE (not needed
- *      when n < 2 or T = 0); its contents are not kept.
- * Each time's valid points are bucket-sorted by x (buckets at least D wide)
- * and every point is tested against the rest of its bucket and the next one.
- * For n <= 12288 this happens in on-chip memory, one workgroup per time (a
- * packing pass, then one launch); larger batches keep the buckets in ws (a
- * range reduction, a histogram, a scan per time, a placement and a sweep).
+ *      (about 12 n T + 4 T n / 4: float x, y, z and a class byte per point; or
+ *      sorted float x, y and satellite index per point and bucket offsets per
+ *      time), else SGP4_E_WORKSPACE (not needed when n < 2 or T = 0); its
+ *      contents are not kept.
+ * Up to 200,000 satellites, each time's valid points are hashed by (x, y) cells
+ * at least D wide in on-chip memory, by sets of x columns for more than 3,072
+ * satellites, and every point is tested against the cells around it (clearing,
+ * packing and sweep kernels; two more for several column sets); larger batches
+ * sort buckets of x in ws (a range reduction, a histogram, a scan per time, a
+ * placement and a sweep).
  * dist_km finite and > 0 (else SGP4_E_ARG); n * T within 2^31 * 256 (else
  * SGP4_E_SIZE). */
 size_t sgp4_screen_workspace_bytes(int64_t n, int64_t T);

@@ -9,24 +9,20 @@
 // dx = x_j - x_i (and so on) formed in double from the stored positions, is an
 // event (i, j, k, sqrt(d2)).
 //
-// Mapping: a packing pass first writes the float x and y of every valid point
-// time-major into the workspace (64 x 64 tiles through LDS, so that both the
-// reads along times and the writes along satellites are coalesced; invalid
-// points get x = +inf).  Then one 1,024-lane workgroup per sample time reads
-// its n (x, y) pairs contiguously and counting-sorts the valid points into
-// buckets of x of width w >= D plus a rounding margin (at most 4,096 buckets
-// over the time's x range; LDS atomics for the counts, one wavefront scan,
-// LDS atomics again for the placement).  A partner j of i with
-// |x_j - x_i| < D then lies in i's bucket or the next one, so each lane takes
-// sorted positions and tests the later points of its bucket and all points
-// of the next (on a spherical shell x is uniformly distributed: about
-// n 2w / 2R candidates).  A candidate whose float x or y differs by D or more,
-// less the rounding margin, is skipped without touching device memory; the
-// rest are tested with the full distance from the stored positions.  The
-// margin, 1.2e-7 (|a| + |b|) for float roundings a, b of two coordinates,
-// bounds the two roundings (2^-24 relative each), so no pair closer than D is
-// pruned.  Workgroups are assigned time blocks per XCD (workgroup w runs on
-// XCD w mod 8), so the workspace rows of neighbouring times share an L2.
+// Two paths.  The usual one (mode 0 and 1): a packing pass writes the float x,
+// y and z of every valid point time-major into the workspace (64 x 64 tiles
+// through LDS, so that both the reads along times and the writes along
+// satellites are coalesced; invalid points get x = +inf), and the largest
+// coordinate of each tile.  Then workgroups of 1,024 lanes each take one sample
+// time and one set of x columns of it: they stream the time's x values, collect
+// the points of their columns in LDS in a hash table of (x, y) cells, and test
+// each point against the cells that can hold a partner.  The other (mode 2, and
+// catalogues beyond kSlabMaxN) sorts buckets of x in device memory.
+//
+// A candidate is taken to the exact test, on the stored positions, when its
+// float coordinates are within D plus a rounding margin in every axis.  The
+// margin, 2.4e-7 R for coordinates up to R, covers the two roundings (2^-24
+// relative each), so no pair closer than D is pruned.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -35,9 +31,7 @@
 
 namespace sgp4mi {
 
-constexpr int kScreenMaxN = 12288;
-constexpr int kScreenBuckets = 4096;
-constexpr int kScreenBlock = 1024;
+constexpr int kScreenMaxN = 12288;  // largest n of mode 1
 
 template <class TR>
 __device__ __forceinline__ double dist2(const TR* __restrict__ r, int64_t P, int64_t pi, int64_t pj) {
@@ -48,154 +42,468 @@ __device__ __forceinline__ double dist2(const TR* __restrict__ r, int64_t P, int
   return (dx * dx + dy * dy) + dz * dz;
 }
 
-// Pack: ws[k * n + i] = (x, y) as floats for a valid point, (+inf, 0) else.
-template <class TR>
-__global__ void __launch_bounds__(256) screen_pack(const TR* __restrict__ r, const uint8_t* __restrict__ err, int64_t n,
-                                                   int64_t T, float2* __restrict__ ws) {
-  __shared__ float2 tile[64][65];
-  const int64_t k0 = int64_t(blockIdx.x) * 64, i0 = int64_t(blockIdx.y) * 64;  // times on x: T may be large
-  const int64_t P = n * T;
-  for (int e = threadIdx.x; e < 4096; e += 256) {
-    const int si = e >> 6, kk = e & 63;  // consecutive lanes: consecutive times of one satellite
-    const int64_t i = i0 + si, k = k0 + kk;
-    float2 v = make_float2(__builtin_inff(), 0.0f);
-    if (i < n && k < T) {
-      const int64_t p = i * T + k;
-      const TR x = r[p], y = r[P + p], z = r[2 * P + p];
-      bool ok = isfinite(double(x)) && isfinite(double(y)) && isfinite(double(z));
-      if (err) ok = ok && (err[p] == 0 || err[p] == 6);
-      if (ok) v = make_float2(float(x), float(y));
-    }
-    tile[si][kk] = v;
-  }
-  __syncthreads();
-  for (int e = threadIdx.x; e < 4096; e += 256) {
-    const int kk = e >> 6, si = e & 63;  // consecutive lanes: consecutive satellites at one time
-    const int64_t i = i0 + si, k = k0 + kk;
-    if (i < n && k < T) ws[k * n + i] = tile[si][kk];
-  }
+// ---------------------------------------------------------- column path --
+// Workspace: the cells per slot of sample times, a class byte per point (rows
+// of T, each padded to whole words), then x, y and z as [T][n] floats.
+constexpr int kSlots = 16;
+// Cells of the sample times of one slot (time tiles of 64 in turn).  near: the
+// float distance in one axis of any pair closer than D; reach: the column width,
+// which also covers the roundings of a coordinate times its reciprocal (2^-24
+// of up to R / w each).  Before slab_geometry, near holds the bits of the
+// largest coordinate R (non-negative floats order as integers).
+struct SlabCells {
+  float near, reach;
+  int32_t left;   // leftmost column
+  int32_t width;  // columns per block
+};
+static_assert(kSlots * sizeof(SlabCells) == 256, "the workspace's first 256 bytes");
+
+struct SlabLayout {
+  SlabCells* cells;
+  uint32_t* cls;  // [T][words]
+  float *x, *y, *z;
+  int64_t words;
+};
+
+__device__ __forceinline__ int slot_of(int64_t k) { return int((k >> 6) & (kSlots - 1)); }
+
+static SlabLayout slab_layout(void* ws, int64_t n, int64_t T) {
+  SlabLayout L;
+  L.words = (n + 3) / 4;
+  L.cells = static_cast<SlabCells*>(ws);
+  L.cls = reinterpret_cast<uint32_t*>(L.cells + kSlots);
+  L.x = reinterpret_cast<float*>(L.cls + L.words * T);
+  L.y = L.x + n * T;
+  L.z = L.y + n * T;
+  return L;
 }
 
+// 13 bytes a point and a little: within the device-memory path's workspace.
+static size_t slab_ws_bytes(int64_t n, int64_t T) {
+  return sizeof(SlabCells) * kSlots + 4 * (size_t((n + 3) / 4) * size_t(T) + 3 * size_t(n) * size_t(T));
+}
+
+__global__ void __launch_bounds__(64) slab_clear(SlabLayout L, unsigned long long* count) {
+  if (threadIdx.x == 0) *count = 0ull;
+  if (threadIdx.x < kSlots) L.cells[threadIdx.x].near = 0.0f;
+}
+
+// Rows (cells along y) are this many column widths tall.  A point looks up its
+// own cell, the one above when it is within reach, and one or two of the next
+// column: tall rows mean fewer lookups, but a cell should rarely hold a point
+// (spread over a sphere, a cell of w by h w holds about 0.6 n h (w / R)^2; the
+// factor aims at 0.15).  Below two widths a point could reach both neighbours.
+__device__ __forceinline__ float row_widths(const SlabCells& c, int32_t n) {
+  const float l = float(c.left);
+  return fminf(fmaxf(0.25f * l * l / float(n), 2.5f), 16.0f);
+}
+
+// A block is `width` columns and belongs to set (block number) mod slabs.  Several
+// blocks per set meet the range of x at equal distances, which evens the sets
+// out for a smooth distribution; but whole columns, a last incomplete round of
+// blocks and the columns next to the blocks weigh the more the narrower they
+// are.  Taken: the width that leaves the fullest set the fewest columns, one
+// block per set counted a sixth more and two a twelfth.
+__device__ __forceinline__ SlabCells cells_of(float R, double D) {
+  SlabCells c;
+  c.near = float((D + 2.4e-7 * double(R)) * (1.0 + 1.0e-6));
+  c.reach = float((D + 8.0e-7 * double(R)) * (1.0 + 1.0e-5));
+  c.left = -int32_t(floorf(R * (1.0f / c.reach))) - 1;
+  c.width = 1;
+  return c;
+}
+
+__global__ void __launch_bounds__(64) slab_geometry(SlabLayout L, double D, int32_t slabs) {
+  if (threadIdx.x >= kSlots) return;
+  SlabCells c = cells_of(L.cells[threadIdx.x].near, D);
+  const uint32_t columns = uint32_t(-2 * c.left);
+  uint32_t best = 0xffffffffu;
+  for (uint32_t m = 1; m <= 6; ++m) {
+    const uint32_t width = (columns + m * slabs - 1) / (m * slabs);
+    const uint32_t blocks = (columns + width - 1) / width;
+    const uint32_t fullest = (blocks + slabs - 1) / slabs * (width + 1) * (m == 1 ? 14 : m == 2 ? 13 : 12);
+    if (fullest < best) {
+      best = fullest;
+      c.width = int32_t(width);
+    }
+  }
+  L.cells[threadIdx.x] = c;
+}
+
+// Column of x and block of a column (both from the left end of the range, so
+// non-negative for every valid point; below 2.7 million, where the quotient by
+// the float reciprocal of the width is exact: the half keeps it 0.5 / width away
+// from whole numbers).
+__device__ __forceinline__ int32_t column_of(float x, float inv_w) { return int32_t(floorf(x * inv_w)); }
+__device__ __forceinline__ uint32_t block_of(int32_t column, int32_t left, float inv_width) {
+  return uint32_t((float(column - left) + 0.5f) * inv_width);
+}
+
+// Pack one 64 x 64 tile.  A lane has its 48 position loads (16 points) out
+// before it uses one: 9,341 x 1,000 floats 54 us for three coordinates, against
+// 60 for two when each point's loads were waited for in turn.
 template <class TR>
-__global__ void __launch_bounds__(kScreenBlock)
-    screen_kernel(const TR* __restrict__ r, const float2* __restrict__ ws, int32_t n, int64_t T, double D,
-                  double D2, int64_t cap, int32_t* __restrict__ pairs, double* __restrict__ dist,
-                  unsigned long long* __restrict__ count) {
-  // LDS: sorted (x, y)[n], sorted satellite index[n], bucket offsets[kScreenBuckets + 1].
-  extern __shared__ float2 smem[];
-  float2* oxy = smem;
-  uint16_t* oidx = reinterpret_cast<uint16_t*>(oxy + n);
-  int32_t* start = reinterpret_cast<int32_t*>(oidx + ((n + 1) & ~1));
-  __shared__ float red_lo[kScreenBlock / 64], red_hi[kScreenBlock / 64];
-  __shared__ double s_x0, s_inv_w;
-  __shared__ int32_t s_nb;
-  // XCD-aware time assignment: grid = 8 * per workgroups; workgroup w = 8 q + x
-  // (on XCD x) takes time x * per + q, a contiguous block of `per` times per XCD.
-  const int64_t per = gridDim.x / 8;
-  const int64_t wg = blockIdx.x;
-  const int64_t k = (wg % 8) * per + wg / 8;
-  if (k >= T) return;  // uniform over the workgroup
-  const int64_t P = int64_t(n) * T;
-  const float2* wk = ws + k * int64_t(n);
+__global__ void __launch_bounds__(256) screen_pack(const TR* __restrict__ r, const uint8_t* __restrict__ err, int64_t n,
+                                                   int64_t T, SlabLayout L) {
+  __shared__ float tile[64][65];
+  __shared__ float wave_max[4];
+  const int64_t k0 = int64_t(blockIdx.x) * 64, i0 = int64_t(blockIdx.y) * 64;  // times on x: T may be large
+  const int64_t P = n * T;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-
-  // Range of the valid x.
-  float lo = __builtin_inff(), hi = -__builtin_inff();
-  for (int32_t s = threadIdx.x; s < n; s += kScreenBlock) {
-    const float x = wk[s].x;
-    if (x < __builtin_inff()) { lo = fminf(lo, x); hi = fmaxf(hi, x); }
+  TR c[3][16];
+  uint8_t code[16];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {  // consecutive lanes: consecutive times of one satellite
+    const int64_t i = i0 + wave + 4 * q, k = k0 + lane;
+    const bool in = i < n && k < T;
+    const int64_t p = in ? i * T + k : 0;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) c[d][q] = in ? r[d * P + p] : TR(0);
+    code[q] = in && err ? err[p] : uint8_t(0);
   }
-  for (int o = 32; o > 0; o >>= 1) {
-    lo = fminf(lo, __shfl_xor(lo, o));
-    hi = fmaxf(hi, __shfl_xor(hi, o));
+  float most = 0.0f;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const float x = float(c[0][q]), y = float(c[1][q]), z = float(c[2][q]);
+    const bool ok = isfinite(x) && isfinite(y) && isfinite(z) && (code[q] == 0 || code[q] == 6);
+    if (ok) most = fmaxf(most, fmaxf(fabsf(x), fmaxf(fabsf(y), fabsf(z))));
+    else c[0][q] = TR(__builtin_inff());
   }
-  if (lane == 0) { red_lo[wave] = lo; red_hi[wave] = hi; }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int v = 1; v < kScreenBlock / 64; ++v) { lo = fminf(lo, red_lo[v]); hi = fmaxf(hi, red_hi[v]); }
-    lo = fminf(red_lo[0], lo);
-    hi = fmaxf(red_hi[0], hi);
-    int32_t nb = 0;
-    double x0 = 0.0, inv_w = 0.0;
-    if (lo <= hi) {
-      const double span = double(hi) - double(lo);
-      const double wmin = (D + 2.4e-7 * fmax(fabs(double(lo)), fabs(double(hi)))) * (1.0 + 1.0e-6);
-      const double w = fmax(wmin, span / double(kScreenBuckets - 1));
-      nb = int32_t(span / w) + 1;
-      if (nb > kScreenBuckets) nb = kScreenBuckets;
-      x0 = lo;
-      inv_w = 1.0 / w;
-    }
-    s_nb = nb; s_x0 = x0; s_inv_w = inv_w;
-  }
-  __syncthreads();
-  const int32_t nb = s_nb;
-  if (nb == 0) return;  // no valid point at this time (uniform)
-  const double x0 = s_x0, inv_w = s_inv_w;
-  auto bucket = [&](float x) {
-    const int32_t b = int32_t((double(x) - x0) * inv_w);
-    return b < nb - 1 ? b : nb - 1;
-  };
-
-  // Counting sort into buckets: start[b + 1] = count of bucket b, scan, place.
-  for (int32_t b = threadIdx.x; b <= nb; b += kScreenBlock) start[b] = 0;
-  __syncthreads();
-  for (int32_t s = threadIdx.x; s < n; s += kScreenBlock) {
-    const float x = wk[s].x;
-    if (x < __builtin_inff()) atomicAdd(&start[bucket(x) + 1], 1);
-  }
-  __syncthreads();
-  if (wave == 0) {  // inclusive scan of start[1..nb] by one wavefront
-    const int32_t chunk = (nb + 63) / 64;
-    const int32_t b0 = 1 + lane * chunk;
-    int32_t sum = 0;
-    for (int32_t b = b0; b < b0 + chunk && b <= nb; ++b) sum += start[b];
-    int32_t incl = sum;
-    for (int o = 1; o < 64; o <<= 1) {
-      const int32_t u = __shfl_up(incl, o);
-      if (lane >= o) incl += u;
-    }
-    int32_t run = incl - sum;
-    for (int32_t b = b0; b < b0 + chunk && b <= nb; ++b) { run += start[b]; start[b] = run; }
-  }
-  __syncthreads();
-  for (int32_t s = threadIdx.x; s < n; s += kScreenBlock) {
-    const float2 v = wk[s];
-    if (v.x < __builtin_inff()) {
-      const int32_t q = atomicAdd(&start[bucket(v.x)], 1);
-      oxy[q] = v;
-      oidx[q] = uint16_t(s);
+  for (int o = 32; o > 0; o >>= 1) most = fmaxf(most, __shfl_xor(most, o));
+  if (lane == 0) wave_max[wave] = most;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    float* const out = d == 0 ? L.x : d == 1 ? L.y : L.z;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 16; ++q) tile[wave + 4 * q][lane] = float(c[d][q]);
+    __syncthreads();
+    const int64_t i = i0 + lane;  // consecutive lanes: consecutive satellites at one time
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const int64_t k = k0 + wave + 4 * q;
+      if (i < n && k < T) out[k * n + i] = tile[lane][wave + 4 * q];
     }
   }
-  __syncthreads();
-  // Now start[b] is the end of bucket b (start[b + 1] before placement).
-  const int32_t m = start[nb - 1];
+  if (threadIdx.x == 0)
+    atomicMax(reinterpret_cast<uint32_t*>(&L.cells[slot_of(k0)].near),
+              __float_as_uint(fmaxf(fmaxf(wave_max[0], wave_max[1]), fmaxf(wave_max[2], wave_max[3]))));
+}
 
-  for (int32_t q = threadIdx.x; q < m; q += kScreenBlock) {
-    const float2 vi = oxy[q];
-    const int32_t i = oidx[q];
-    const int32_t b = bucket(vi.x);
-    const int32_t end = b + 1 < nb ? start[b + 1] : start[b];
-    const double xi = vi.x, yi = vi.y;
-    const int64_t pi = int64_t(i) * T + k;
-    for (int32_t q2 = q + 1; q2 < end; ++q2) {
-      const float2 vj = oxy[q2];
-      const double xj = vj.x, yj = vj.y;
-      if (!(fabs(xj - xi) < D + 1.2e-7 * (fabs(xi) + fabs(xj)))) continue;
-      if (!(fabs(yj - yi) < D + 1.2e-7 * (fabs(yi) + fabs(yj)))) continue;
-      const int32_t j = oidx[q2];
-      const int64_t pj = int64_t(j) * T + k;
-      const double d2 = dist2(r, P, pi, pj);
-      if (d2 < D2) {
-        const unsigned long long e = atomicAdd(count, 1ull);
-        if (int64_t(e) < cap) {
-          pairs[3 * e] = i < j ? i : j;
-          pairs[3 * e + 1] = i < j ? j : i;
-          pairs[3 * e + 2] = int32_t(k);
-          dist[e] = sqrt(d2);
+// Class byte of every point: its column set and, in bit 7, whether its column is
+// the first of its block; invalid points 0xff.
+// The column sets' workgroups then test four points per instruction.
+__global__ void __launch_bounds__(256) screen_class(SlabLayout L, int32_t n, int64_t T, int32_t slabs) {
+  const int64_t per = (L.words + 255) / 256;  // workgroups per sample time
+  const int64_t k = blockIdx.x / per;
+  const int64_t word = (blockIdx.x - k * per) * 256 + threadIdx.x;
+  if (word >= L.words) return;
+  const SlabCells g = L.cells[slot_of(k)];
+  const float inv_w = 1.0f / g.reach, inv_width = 1.0f / float(g.width);
+  uint32_t out = 0;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int64_t i = 4 * word + e;
+    const float x = i < n ? L.x[k * n + i] : __builtin_inff();
+    const int32_t c = column_of(x, inv_w);
+    const uint32_t b = block_of(c, g.left, inv_width);
+    const uint32_t first = int32_t(b) * g.width == c - g.left ? 0x80u : 0u;
+    const uint32_t v = x < __builtin_inff() ? b % uint32_t(slabs) | first : 0xffu;
+    out |= v << (8 * e);
+  }
+  L.cls[k * L.words + word] = out;
+}
+
+// Points per table, hash heads, occupancy bits, pending walks and buffered
+// events of a workgroup: 79 KiB of LDS, two workgroups (32 wavefronts) per
+// compute unit.
+constexpr int kSlabBlock = 1024;
+constexpr int kSlabPoints = 3072;
+constexpr int kSlabHeads = 2048;
+constexpr int kSlabBits = 32768;
+constexpr int kSlabWalks = 1536;
+constexpr int kSlabEvents = 256;
+static_assert(kSlabPoints <= 4096, "a pending walk holds 12 bits of entry and 2 of cell");
+// Lanes of mask m below this one.
+__device__ __forceinline__ int32_t rank_in(unsigned long long m) {
+  return int32_t(__builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u)));
+}
+
+// Work item u: sample time u / slabs and column set u % slabs.  Columns of width
+// w > D + margins run over all x; blocks of 2^shift columns belong to the column
+// sets in turn, so that any smooth distribution of x spreads evenly without a
+// look at it.  A set's table holds its own points and, for the pairs across a
+// block's upper edge, those of the next block's first column.  Each pair is met
+// once: from its lower column, from its lower row within a column, once within
+// a cell.  A set whose points exceed the table (all points in a few columns,
+// say) takes the time's satellites in runs: a table per run, every own point of
+// the time tested against each.
+//
+// Bound by VALU issue: the stream of class bytes (every set reads its time's:
+// five instructions a point, half of the whole at 100,000 satellites) and the
+// cells' lookups.  One workgroup per time with a bucket sort by x in LDS took 219
+// us at 9,341 x 1,000, this kernel 140; buckets of x in device memory 2.6 ms for
+// the sweep alone at 100,000 x 144, with 110 candidates per point, this kernel
+// 0.59 ms.
+//
+// kOne: one set holds every point (n <= kSlabPoints): no classes, no geometry
+// kernel, no overflow.
+template <class TR, bool kOne>
+__global__ void __launch_bounds__(kSlabBlock, 8)
+    screen_slab_kernel(const TR* __restrict__ r, SlabLayout L, int32_t n, int64_t T, double D, double D2, int64_t cap,
+                       int32_t slabs, int32_t* __restrict__ pairs, double* __restrict__ dist,
+                       unsigned long long* __restrict__ count) {
+  __shared__ float4 point[kSlabPoints];  // x, y, z and the chain's next entry
+  __shared__ int32_t owner[kSlabPoints];  // satellite; ~satellite for the next block's points
+  __shared__ int32_t head[kSlabHeads];
+  __shared__ uint32_t bits[kSlabBits / 32];  // cells (by a finer hash) that hold a point
+  __shared__ uint16_t walks[kSlabWalks];
+  __shared__ int2 event_pair[kSlabEvents];
+  __shared__ double event_dist[kSlabEvents];
+  __shared__ int32_t held, events, pending;
+  __shared__ unsigned long long event_base;
+  const int lane = threadIdx.x & 63;
+  const int64_t P = int64_t(n) * T, total = T * slabs;
+  // workgroup w runs on XCD w mod 8: each XCD takes a contiguous run of items,
+  // so the workgroups of one time share an L2
+  const int64_t per = (total + 7) / 8;
+  for (int64_t v = blockIdx.x; v < 8 * per; v += gridDim.x) {
+    const int64_t u = (v & 7) * per + (v >> 3);
+    if ((v >> 3) >= per || u >= total) continue;  // uniform over the workgroup
+    const int64_t k = u / slabs;
+    const int32_t slab = int32_t(u - k * slabs);
+    const float* const X = L.x + k * int64_t(n);
+    const float* const Y = L.y + k * int64_t(n);
+    const float* const Z = L.z + k * int64_t(n);
+
+    const SlabCells g = kOne ? cells_of(L.cells[slot_of(k)].near, D) : L.cells[slot_of(k)];
+    const float near = g.near, reach = g.reach;
+    const float inv_w = 1.0f / reach, inv_h = inv_w / row_widths(g, n), inv_width = 1.0f / float(g.width);
+    auto column = [&](float x) { return column_of(x, inv_w); };
+    auto row = [&](float y) { return int32_t(floorf(y * inv_h)); };
+    // a cell's hash: its upper 11 bits are the head, its upper 15 the occupancy bit
+    auto cell_hash = [&](int32_t c, int32_t b) { return uint32_t(c) * 0x9e3779b1u ^ uint32_t(b) * 0x85ebca77u; };
+    auto bucket = [&](int32_t c, int32_t b) { return cell_hash(c, b) >> (32 - 11); };
+    auto occupied = [&](int32_t c, int32_t b) {
+      const uint32_t h = cell_hash(c, b) >> (32 - 15);
+      return ((bits[h >> 5] >> (h & 31)) & 1u) != 0;
+    };
+    static_assert(kSlabHeads == 1 << 11 && kSlabBits == 1 << 15, "hash bits");
+    // 2: a column of the set's own; 1: the first column of the block after an own
+    // one; 0: neither
+    auto belongs = [&](int32_t c) {
+      const uint32_t b = block_of(c, g.left, inv_width), set = b % uint32_t(slabs);
+      if (set == uint32_t(slab)) return 2;
+      return set == uint32_t((slab + 1) % slabs) && int32_t(b) * g.width == c - g.left ? 1 : 0;
+    };
+
+    // Table of the set's points among satellites [lo, hi), lo a multiple of four;
+    // returns how many the class bytes name (past kSlabPoints none is stored).
+    // The stream only notes which satellites belong; coordinates and chains are
+    // left to full wavefronts afterwards.
+    const uint32_t own_class = uint32_t(slab) * 0x01010101u;
+    const uint32_t next_class = uint32_t((slab + 1) % slabs) * 0x01010101u;
+    const uint32_t* const classes = L.cls + k * L.words;
+    auto build = [&](int32_t lo, int32_t hi) {
+      __syncthreads();
+      for (int q = threadIdx.x; q < kSlabHeads; q += kSlabBlock) head[q] = -1;
+      for (int q = threadIdx.x; q < kSlabBits / 32; q += kSlabBlock) bits[q] = 0u;
+      if (threadIdx.x == 0) held = pending = 0;
+      __syncthreads();
+      const int32_t w1 = kOne ? 0 : (hi + 3) >> 2;
+      for (int32_t w0 = lo >> 2; w0 < w1; w0 += 4 * kSlabBlock) {
+        uint32_t word[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int32_t w = w0 + e * kSlabBlock + int32_t(threadIdx.x);
+          word[e] = w < w1 ? classes[w] : 0xffffffffu;
+        }
+        // bit 8 b + e: point b of word e belongs (a byte of seven bits plus 0x7f
+        // reaches bit 7 unless it is zero)
+        uint32_t flags = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t low = word[e] & 0x7f7f7f7fu;
+          const uint32_t own = ~((low ^ own_class) + 0x7f7f7f7fu), next = ~((low ^ next_class) + 0x7f7f7f7fu) & word[e];
+          flags |= ((own | next) & 0x80808080u) >> (7 - e);
+        }
+        if (__ballot(flags != 0) == 0) continue;
+        // places in the list: a prefix sum of the lanes' counts, bit by bit
+        const int32_t mine = __popc(flags);
+        int32_t before = 0, found = 0;
+#pragma unroll
+        for (int e = 0; e < 5; ++e) {
+          const unsigned long long m = __ballot((mine >> e) & 1);
+          if (m == 0) continue;
+          before += rank_in(m) << e;
+          found += __popcll(m) << e;
+        }
+        int32_t at = 0;
+        if (lane == 0) at = atomicAdd(&held, found);
+        at = __builtin_amdgcn_readfirstlane(at) + before;
+        while (flags != 0) {
+          const int f = __ffs(flags) - 1;
+          flags &= flags - 1;
+          if (at < kSlabPoints) owner[at] = 4 * (w0 + (f & 7) * kSlabBlock + int32_t(threadIdx.x)) + (f >> 3);
+          ++at;
+        }
+      }
+      __syncthreads();
+      const int32_t all = kOne ? n : held, m = all < kSlabPoints ? all : kSlabPoints;
+      for (int32_t q = threadIdx.x; q < m; q += kSlabBlock) {
+        const int32_t i = kOne ? q : owner[q];
+        const float x = i < hi ? X[i] : __builtin_inff();
+        const int32_t c = column(x);
+        const int mine = !(x < __builtin_inff()) ? 0 : kOne ? 2 : belongs(c);
+        if (mine == 0) {
+          owner[q] = ~i;  // not of the set after all: in no chain
+          continue;
+        }
+        const float y = Y[i], z = Z[i];
+        const uint32_t h = cell_hash(c, row(y));
+        atomicOr(&bits[h >> (32 - 10)], 1u << ((h >> (32 - 15)) & 31));
+        const int32_t next = atomicExch(&head[h >> (32 - 11)], q);
+        point[q] = make_float4(x, y, z, __int_as_float(next));
+        if (kOne || mine == 1) owner[q] = mine == 1 ? ~i : i;
+      }
+      __syncthreads();
+      return all;
+    };
+
+    auto report = [&](int32_t i, int32_t j, double d2) {
+      const int32_t a = i < j ? i : j, b = i < j ? j : i;
+      const double d = sqrt(d2);
+      const int32_t e = atomicAdd(&events, 1);
+      if (e < kSlabEvents) {
+        event_pair[e] = make_int2(a, b);
+        event_dist[e] = d;
+      } else {
+        const unsigned long long g = atomicAdd(count, 1ull);
+        if (int64_t(g) < cap) {
+          pairs[3 * g] = a;
+          pairs[3 * g + 1] = b;
+          pairs[3 * g + 2] = int32_t(k);
+          dist[g] = d;
+        }
+      }
+    };
+
+    // Candidates of point (x, y, z) of satellite i from entry q on along a chain,
+    // in cell (c, b); after: only satellites after i (its own cell's pairs).
+    auto walk = [&](int32_t q, int32_t c, int32_t b, bool after, float x, float y, float z, int32_t i) {
+      while (q >= 0) {
+        const float4 o = point[q];
+        if (fabsf(o.x - x) <= near && fabsf(o.y - y) <= near && fabsf(o.z - z) <= near && column(o.x) == c &&
+            row(o.y) == b) {
+          const int32_t w = owner[q], j = w < 0 ? ~w : w;
+          if (!after || j > i) {
+            const double d2 = dist2(r, P, int64_t(i) * T + k, int64_t(j) * T + k);
+            if (d2 < D2) report(i, j, d2);
+          }
+        }
+        q = __float_as_int(o.w);
+      }
+    };
+    // Walk e of table entry q: 0 its own chain from its next entry on (a pair in
+    // one bucket is met once, from the later entry), 1 the cell above, 2 the next
+    // column's cell, 3 that column's cell above or below, whichever is in reach
+    // (a row is more than two reaches tall).
+    auto table_walk = [&](int32_t q, int e) {
+      const float4 o = point[q];
+      const int32_t c = column(o.x), b = row(o.y), above = row(o.y + reach);
+      const int32_t side = above != b ? above : row(o.y - reach);
+      const int32_t cc = c + (e >> 1), bb = e == 0 || e == 2 ? b : e == 1 ? above : side;
+      walk(e == 0 ? __float_as_int(o.w) : head[bucket(cc, bb)], cc, bb, false, o.x, o.y, o.z, owner[q]);
+    };
+
+    if (threadIdx.x == 0) events = 0;
+    const int32_t m = build(0, n);
+    if (kOne || m <= kSlabPoints) {
+      // Most cells that could hold a partner are empty, and a wavefront that
+      // walks chains for a few of its lanes takes as long as for all: so the
+      // walks that the occupancy bits leave are listed first, then taken by full
+      // wavefronts.
+      const int32_t rounds = (m + kSlabBlock - 1) / kSlabBlock;
+      for (int32_t t0 = 0; t0 < rounds; ++t0) {
+        const int32_t q = t0 * kSlabBlock + threadIdx.x;
+        bool go[4] = {false, false, false, false};
+        if (q < m && owner[q] >= 0) {
+          const float4 o = point[q];
+          const int32_t c = column(o.x), b = row(o.y), above = row(o.y + reach);
+          const int32_t side = above != b ? above : row(o.y - reach);
+          go[0] = __float_as_int(o.w) >= 0;
+          go[1] = above != b && occupied(c, above);
+          go[2] = occupied(c + 1, b);
+          go[3] = side != b && occupied(c + 1, side);
+        }
+        unsigned long long g[4];
+        int32_t found = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          g[e] = __ballot(go[e]);
+          found += __popcll(g[e]);
+        }
+        if (found == 0) continue;
+        int32_t at = 0;
+        if (lane == 0) at = atomicAdd(&pending, found);
+        at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          if (g[e] == 0) continue;
+          const int32_t w = at + rank_in(g[e]);
+          at += __popcll(g[e]);
+          if (!go[e]) continue;
+          if (w < kSlabWalks) walks[w] = uint16_t(q | (e << 12));
+          else table_walk(q, e);
+        }
+      }
+      __syncthreads();
+      const int32_t listed = pending < kSlabWalks ? pending : kSlabWalks;
+      for (int32_t w = threadIdx.x; w < listed; w += kSlabBlock) table_walk(walks[w] & 0xfff, walks[w] >> 12);
+    } else {
+      // runs of satellites whose points fit a table (runs of kSlabPoints always do)
+      int32_t run = int32_t(int64_t(n) * kSlabPoints / (int64_t(m) * 5 / 4));
+      run = (run < kSlabPoints ? kSlabPoints : run) & ~3;
+      for (int32_t lo = 0; lo < n;) {
+        const int32_t hi = n - lo < run ? n : lo + run;
+        if (build(lo, hi) > kSlabPoints) {  // the same for all lanes
+          run = (run / 2 < kSlabPoints ? kSlabPoints : run / 2) & ~3;
+          continue;
+        }
+        lo = hi;
+        for (int32_t w = threadIdx.x; w < int32_t(L.words); w += kSlabBlock) {
+          const uint32_t word = classes[w];
+          for (uint32_t f = ~(((word & 0x7f7f7f7fu) ^ own_class) + 0x7f7f7f7fu) & 0x80808080u; f != 0; f &= f - 1) {
+            const int32_t i = 4 * w + ((__ffs(f) - 1) >> 3);
+            const float x = i < n ? X[i] : __builtin_inff();
+            if (!(x < __builtin_inff()) || belongs(column(x)) != 2) continue;
+            const float y = Y[i], z = Z[i];
+            const int32_t c = column(x), b = row(y), above = row(y + reach);
+            const int32_t side = above != b ? above : row(y - reach);
+            for (int e = 0; e < 4; ++e) {
+              const int32_t cc = c + (e >> 1), bb = e == 0 || e == 2 ? b : e == 1 ? above : side;
+              if ((e == 1 || e == 3) && bb == b) continue;
+              walk(head[bucket(cc, bb)], cc, bb, e == 0, x, y, z, i);
+            }
+          }
         }
       }
     }
+    __syncthreads();
+    // the buffered events: one addition to the device counter per item
+    const int32_t ne = events < kSlabEvents ? events : kSlabEvents;
+    if (threadIdx.x == 0 && ne > 0) event_base = atomicAdd(count, (unsigned long long)ne);
+    __syncthreads();
+    for (int32_t e = threadIdx.x; e < ne; e += kSlabBlock) {
+      const int64_t g = int64_t(event_base) + e;
+      if (g < cap) {
+        pairs[3 * g] = event_pair[e].x;
+        pairs[3 * g + 1] = event_pair[e].y;
+        pairs[3 * g + 2] = int32_t(k);
+        dist[g] = event_dist[e];
+      }
+    }
+    __syncthreads();
   }
 }
 
@@ -205,16 +513,8 @@ __global__ void screen_clear(unsigned long long* count) {
 
 int screen_max_n() { return kScreenMaxN; }
 
-// Dynamic LDS of the screening kernel: 10 n bytes of sorted points plus the
-// bucket offsets (136 KiB at n = 12,288).
-static size_t screen_lds_bytes(int64_t n) {
-  return size_t(n) * 8 + size_t((n + 1) & ~int64_t(1)) * 2 + size_t(kScreenBuckets + 1) * 4;
-}
-
-// ------------------------------------------------------- any-n (global) path --
-// The same bucket sort and sweep with the buckets in device memory, for
-// batches whose points do not fit one workgroup's LDS.  Buckets of x span a
-// range [-R, R] with R the largest |x| of any valid point (one reduction over
+// ---------------------------------------------------- device-memory path --
+// A bucket sort of x in device memory and a sweep.  Buckets of x span a range [-R, R] with R the largest |x| of any valid point (one reduction over
 // the batch), nb = n / 4 of them at most, width w >= D plus the rounding
 // margin of R (fewer, wider buckets when the range is small).  Per time k:
 // counts[k][b] (histogram, then offsets by an in-place scan, then ends after
@@ -294,7 +594,15 @@ __global__ void __launch_bounds__(256) gscreen_range(const TR* __restrict__ r, c
     if (valid_point(r, err, P, p, &x, &y)) m = fmaxf(m, fabsf(x));
   }
   for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-  if ((threadIdx.x & 63) == 0) atomicMax(&L.hdr->rbits, __float_as_uint(m));
+  // one address for the whole batch: an atomic takes ~11 ns, so one per
+  // workgroup of a grid that just fills the chip (one per wavefront of 16,384
+  // workgroups took 754 us at 100,000 x 144)
+  __shared__ float wave_max[4];
+  if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0)
+    atomicMax(&L.hdr->rbits,
+              __float_as_uint(fmaxf(fmaxf(wave_max[0], wave_max[1]), fmaxf(wave_max[2], wave_max[3]))));
 }
 
 __global__ void gscreen_buckets(GLayout L, double D) {
@@ -426,7 +734,7 @@ static hipError_t screen_global(const TR* r, const uint8_t* err, int64_t n, int6
   const int64_t cells = T * (L.nbmax + 1);
   hipLaunchKernelGGL(gscreen_clear, dim3(unsigned(std::min<int64_t>((cells + 255) / 256, 65536))), dim3(256), 0, s,
                      L, T);
-  hipLaunchKernelGGL(gscreen_range<TR>, dim3(unsigned(std::min<int64_t>((P + 255) / 256, 16384))), dim3(256), 0, s,
+  hipLaunchKernelGGL(gscreen_range<TR>, dim3(unsigned(std::min<int64_t>((P + 255) / 256, 2048))), dim3(256), 0, s,
                      r, err, P, L);
   hipLaunchKernelGGL(gscreen_buckets, dim3(1), dim3(64), 0, s, L, D);
   hipLaunchKernelGGL(gscreen_count<TR>, dim3(gp), dim3(256), 0, s, r, err, T, P, L);
@@ -436,56 +744,72 @@ static hipError_t screen_global(const TR* r, const uint8_t* err, int64_t n, int6
   return hipGetLastError();
 }
 
-// Workspace of the two paths: the LDS path packs 8 bytes per point; the
-// global path holds the header, the per-time bucket offsets and 12 bytes per
-// point of sorted (x, y) and satellite index.
+// Workspace of the two paths: the larger one's, the device-memory path's (the
+// header, the per-time bucket offsets and 12 bytes per point).
 size_t screen_ws_bytes(int64_t n, int64_t T) {
-  const size_t lds = size_t(n) * size_t(T) * sizeof(float2);
+  const size_t slab = slab_ws_bytes(n, T);
   const size_t glob = global_ws_bytes(n, T);
-  return lds > glob ? lds : glob;  // enough for either path
+  return slab > glob ? slab : glob;  // enough for either path
 }
 
-// Largest n * T the global path indexes (grids of 256-lane workgroups).
+// Largest n * T the device-memory path indexes (grids of 256-lane workgroups).
 bool screen_global_fits(int64_t n, int64_t T) {
   return n <= 0x7fffffff && n * T <= int64_t(0x7fffffff) * 256 && T <= 0x7fffffff;
 }
 
-// mode 0: the LDS path when n <= kScreenMaxN, else the global path; 1: LDS
-// path (the caller checks n); 2: global path.
+// Catalogues beyond this take the device-memory path: every column set streams
+// the whole time's class bytes, which grows with the square of n, and a class
+// byte numbers up to 127 sets (0x7f is left to invalid points).
+constexpr int64_t kSlabMaxN = 200000;
+
+// Column sets per time: a table has room for 30% more than a set's even share,
+// and a further quarter per 100,000 satellites, since the sets then have few
+// columns (28 at 100,000 satellites and 10 km).  The fullest set of the test
+// constellation's, 2 to 10 km, holds 2,300 to 2,750 of 3,072 points from 20,000
+// to 200,000 satellites; one that overflows works in runs, at about twice the
+// time.
+static int32_t slab_count(int64_t n) {
+  return n <= kSlabPoints ? 1 : int32_t((n * 13 / 10 + n * n / 400000 + kSlabPoints - 1) / kSlabPoints);
+}
+
+template <class TR>
+static hipError_t screen_slabs(const TR* r, const uint8_t* err, int64_t n, int64_t T, double D, int64_t cap,
+                               int32_t* pairs, double* dist, unsigned long long* count, void* ws, hipStream_t s) {
+  const SlabLayout L = slab_layout(ws, n, T);
+  const int32_t slabs = slab_count(n);
+  hipLaunchKernelGGL(slab_clear, dim3(1), dim3(64), 0, s, L, count);
+  hipLaunchKernelGGL(screen_pack<TR>, dim3(unsigned((T + 63) / 64), unsigned((n + 63) / 64)), dim3(256), 0, s, r, err,
+                     n, T, L);
+  const int64_t items = (T * slabs + 7) / 8 * 8;
+  const dim3 grid(unsigned(std::min<int64_t>(items, (int64_t(1) << 32) / kSlabBlock - 8)));
+  if (slabs == 1) {
+    hipLaunchKernelGGL((screen_slab_kernel<TR, true>), grid, dim3(kSlabBlock), 0, s, r, L, int32_t(n), T, D, D * D,
+                       cap, slabs, pairs, dist, count);
+  } else {
+    hipLaunchKernelGGL(slab_geometry, dim3(1), dim3(64), 0, s, L, D, slabs);
+    hipLaunchKernelGGL(screen_class, dim3(unsigned(T * ((L.words + 255) / 256))), dim3(256), 0, s, L, int32_t(n), T,
+                       slabs);
+    hipLaunchKernelGGL((screen_slab_kernel<TR, false>), grid, dim3(kSlabBlock), 0, s, r, L, int32_t(n), T, D, D * D,
+                       cap, slabs, pairs, dist, count);
+  }
+  return hipGetLastError();
+}
+
+// mode 0: the column path up to kSlabMaxN satellites, else the device-memory
+// path; 1: the column path (the caller checks n); 2: the device-memory path.
 hipError_t launch_screen(const void* r, bool fp64, const uint8_t* err, int64_t n, int64_t T, double D, int64_t cap,
                          int32_t* pairs, double* dist, unsigned long long* count, void* ws, int mode, hipStream_t s) {
-  hipLaunchKernelGGL(screen_clear, dim3(1), dim3(64), 0, s, count);
-  if (n < 2 || T == 0) return hipGetLastError();
-  if (mode == 2 || (mode == 0 && n > kScreenMaxN)) {
+  const bool global = mode == 2 || (mode == 0 && n > kSlabMaxN);
+  if (n < 2 || T == 0 || global) {
+    hipLaunchKernelGGL(screen_clear, dim3(1), dim3(64), 0, s, count);
+    if (n < 2 || T == 0) return hipGetLastError();
+  }
+  if (global) {
     if (fp64) return screen_global(static_cast<const double*>(r), err, n, T, D, cap, pairs, dist, count, ws, s);
     return screen_global(static_cast<const float*>(r), err, n, T, D, cap, pairs, dist, count, ws, s);
   }
-  float2* w = static_cast<float2*>(ws);
-  const dim3 pg(unsigned((T + 63) / 64), unsigned((n + 63) / 64));
-  if (fp64)
-    hipLaunchKernelGGL(screen_pack<double>, pg, dim3(256), 0, s, static_cast<const double*>(r), err, n, T, w);
-  else
-    hipLaunchKernelGGL(screen_pack<float>, pg, dim3(256), 0, s, static_cast<const float*>(r), err, n, T, w);
-  const unsigned grid = unsigned(8 * ((T + 7) / 8));
-  const size_t lds = screen_lds_bytes(n);
-  static bool attr_set = false;
-  if (!attr_set) {
-    const int most = int(screen_lds_bytes(kScreenMaxN));
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&screen_kernel<double>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, most);
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(&screen_kernel<float>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, most);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
-  if (fp64)
-    hipLaunchKernelGGL(screen_kernel<double>, dim3(grid), dim3(kScreenBlock), lds, s, static_cast<const double*>(r),
-                       w, int32_t(n), T, D, D * D, cap, pairs, dist, count);
-  else
-    hipLaunchKernelGGL(screen_kernel<float>, dim3(grid), dim3(kScreenBlock), lds, s, static_cast<const float*>(r), w,
-                       int32_t(n), T, D, D * D, cap, pairs, dist, count);
-  return hipGetLastError();
+  if (fp64) return screen_slabs(static_cast<const double*>(r), err, n, T, D, cap, pairs, dist, count, ws, s);
+  return screen_slabs(static_cast<const float*>(r), err, n, T, D, cap, pairs, dist, count, ws, s);
 }
 
 // ------------------------------------------------------------- no-alloc --
