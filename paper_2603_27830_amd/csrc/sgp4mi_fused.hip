@@ -5,31 +5,37 @@
 // of this library instead writes a 512-byte record per satellite and reads it
 // back.  For short time lists (a catalogue propagated to one or a few epochs)
 // the record round trip and the second launch dominate, so this kernel keeps
-// the record on chip:
-//   workgroup = 64 satellites x tt times (tt <= kFusedTT), 64 * tt lanes;
-//   wavefront 0 initialises the 64 satellites, one per lane, and leaves the
-//   constants in LDS (tt = 1: in the lane's own registers);
-//   every lane then propagates one (satellite, time) point, lanes ordered
-//   satellite-major so the stores of a workgroup are contiguous when tt = T.
-// Longer time lists take a grid of ceil(T / tt) workgroups per 64 satellites,
-// each repeating the 64 initialisations (one wavefront of initialisation per
-// tt wavefronts of propagation); the entry point sends such batches to the
-// two-stage path when the caller supplies a record workspace.
+// the constants on chip: the first kFusedSats lanes of a workgroup initialise a
+// satellite each and leave the constants that their precision reads in LDS;
+// then all lanes take the workgroup's points in output order, so that stores
+// are contiguous whatever the number of times.  Batches of few satellites spread
+// their times over the grid's y extent, each workgroup repeating the
+// initialisation (compute units would otherwise idle).
 #include "sgp4mi_initcore.h"
 #include "sgp4mi_out.h"
+
+#include <algorithm>
 
 namespace sgp4mi {
 
 constexpr int kFusedTT = 16;
+// Satellites and lanes of a workgroup: half of its wavefronts initialise while
+// the others wait, and several workgroups on a compute unit fill the gaps.
+// Measured at 300,007 x 19 mixed (1M x 8 FP64): 64 and 128 lanes 65 (206) us, 128
+// and 256 66 (208), 256 and 256 72 (192, but 23 against 16 at 30,000 x 8), 128 and
+// 512 72 (242).
+constexpr int kFusedSats = 64;
+constexpr int kFusedBlock = 128;
 
 struct FusedArgs {
   int64_t n, T;
   const double* elem;   // [8][n]
   const double* t;      // [T]
   uint8_t* user_flags;  // nullable
-  double mu, radius, j2, j3, j4;
+  GravIn grav;
+  double vkms;
   double ref_day;       // reference instant of the epoch row, days after JD 2415020.0
-  uint32_t tt;
+  int64_t per;          // times per workgroup
 };
 
 // The satellite's constants as the two-stage path reads them from its slot:
@@ -58,92 +64,195 @@ __device__ __forceinline__ SatC<TS, TP> sat_of(const double* x, uint32_t info, c
 }
 
 // Gravity scalars as the initialisation kernel writes them to the record
-// header (the same expressions, so both paths see the same values).
+// header.
 __device__ __forceinline__ Grav grav_of(const FusedArgs& a) {
   Grav g;
-  g.ke = 60.0 / sqrt(a.radius * a.radius * a.radius / a.mu);
-  g.radius = a.radius;
-  g.vkms = a.radius * g.ke / 60.0;
-  g.k2 = 0.5 * a.j2;
-  g.j3oj2 = (a.j3 == 0.0) ? 0.0 : a.j3 / a.j2;
-  g.radius_f = float(a.radius);
-  g.vkms_f = float(a.radius * g.ke / 60.0);
-  g.k2_f = float(0.5 * a.j2);
+  g.ke = a.grav.ke;
+  g.radius = a.grav.radius;
+  g.vkms = a.vkms;
+  g.k2 = 0.5 * a.grav.j2;
+  g.j3oj2 = a.grav.j3oj2;
+  g.radius_f = float(a.grav.radius);
+  g.vkms_f = float(a.vkms);
+  g.k2_f = float(0.5 * a.grav.j2);
   return g;
 }
 
-// Initialisation of satellite i into rec (kNRec doubles) and, for a
-// propagated deep-space satellite, deep (kNDeep doubles); returns the info word.
-__device__ __forceinline__ uint32_t init_sat(const FusedArgs& a, const Grav& g, int64_t i, double* rec, double* deep,
-                                             bool write_flags) {
-  double el[7];
+// Initialisation of satellite i into rec (kNRec doubles); returns the info word
+// and, with it, the elements and the epoch for a deep-space satellite's terms.
+__device__ __forceinline__ uint32_t init_sat(const FusedArgs& a, const Grav& g, int64_t i, double* rec, double* el,
+                                             double* epoch) {
 #pragma unroll
   for (int k = 0; k < 7; ++k) el[k] = a.elem[k * a.n + i];
-  const double epoch = a.elem[7 * a.n + i];
-  const double j3oj2 = (a.j3 == 0.0) ? 0.0 : a.j3 / a.j2;
-  GravIn gi{a.radius, a.j2, a.j4, g.ke, j3oj2};
+  *epoch = a.elem[7 * a.n + i];
   uint32_t code;
   bool isimp, dsp;
-  init_record<double>(gi, el, rec, &code, &isimp, &dsp);
-  rec[kEpochMin] = 1440.0 * epoch;
-  if (dsp && code == 0) init_deep(el, rec, g.ke, a.ref_day + epoch, deep);
-  if (write_flags && a.user_flags) {
-    uint8_t f = 0;
-    if (dsp) f |= 1;
-    if (isimp) f |= 2;
-    if (code == 1 || code == 2) f |= 4;
-    if (dsp && code == 0 && deep[kDRes] != 0.0) f |= 8;
-    a.user_flags[i] = f;
-  }
+  init_record<double>(a.grav, el, rec, &code, &isimp, &dsp);
+  rec[kEpochMin] = 1440.0 * *epoch;
   return code | (isimp ? kInfoIsimp : 0u) | (dsp ? kInfoDeep : 0u);
 }
 
-// tt = 1: one wavefront per 64 satellites, each lane initialises and
-// propagates its own satellite to the single time.
+__device__ __forceinline__ void put_flags(const FusedArgs& a, int64_t i, uint32_t info, bool resonant) {
+  if (!a.user_flags || blockIdx.y != 0) return;
+  const uint32_t code = info & kInfoCodeMask;
+  uint8_t f = 0;
+  if (info & kInfoDeep) f |= 1;
+  if (info & kInfoIsimp) f |= 2;
+  if (code == 1 || code == 2) f |= 4;
+  if (resonant) f |= 8;
+  a.user_flags[i] = f;
+}
+
+// A deep-space satellite's times [t0, t1), initialised anew and written point by
+// point: apart from the near-Earth lanes, whose registers it would otherwise
+// share (its terms hold more values than the constants of a near-Earth loop).
 template <class TS, class TP, bool kOff32>
-__global__ void __launch_bounds__(64) fused_one_kernel(FusedArgs a, Out<TP, kOff32> out) {
+__device__ __forceinline__ void fused_deep(const FusedArgs& a, const Grav& g, int64_t i, int64_t t0, int64_t t1,
+                                           const Out<TP, kOff32>& out) {
+  double rec[kNRec], deep[kNDeep], el[7], epoch;
+  const uint32_t info = init_sat(a, g, i, rec, el, &epoch);
+  init_deep(el, rec, g.ke, a.ref_day + epoch, deep);
+  put_flags(a, i, info, deep[kDRes] != 0.0);
+  const SatC<TS, TP> c = sat_of<TS, TP>(rec, info, deep);
+  for (int64_t j = t0; j < t1; ++j) {
+    asm volatile("" ::: "memory");  // the deep-space terms stay in memory between points
+    PointState<TP> s;
+    const uint32_t code = deep_point<TS, TP>(c, g, a.t[j], s);
+    out.put(i * a.T + j, code, s);
+  }
+}
+
+// One time: each lane initialises and propagates its own satellite.  Bound by
+// VALU issue: 1M satellites FP64 43 -> 38 us with the reciprocals and roots of
+// init_record; four wavefronts per SIMD (128 registers) spill and take 42.
+template <class TS, class TP, bool kOff32>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3)))
+    fused_one_kernel(FusedArgs a, Out<TP, kOff32> out) {
   const int64_t i = int64_t(blockIdx.x) * 64 + threadIdx.x;
   if (i >= a.n) return;
   const Grav g = grav_of(a);
-  double rec[kNRec], deep[kNDeep];
-  const uint32_t info = init_sat(a, g, i, rec, deep, true);
-  const SatC<TS, TP> c = sat_of<TS, TP>(rec, info, deep);
-  PointState<TP> s;
-  const uint32_t code = (c.info & kInfoDeep) ? deep_point<TS, TP>(c, g, a.t[0], s) : sgp4_point<TS, TP>(c, g, a.t[0], s);
-  out.put(i, code, s);
-}
-
-template <class TS, class TP, bool kOff32>
-__global__ void __launch_bounds__(64 * kFusedTT) fused_kernel(FusedArgs a, Out<TP, kOff32> out) {
-  __shared__ double lrec[kNRec][64];
-  __shared__ double ldeep[64][kNDeep];
-  __shared__ uint32_t linfo[64];
-  const int64_t i0 = int64_t(blockIdx.x) * 64;
-  const Grav g = grav_of(a);
-  if (threadIdx.x < 64) {
-    const int64_t i = i0 + threadIdx.x;
-    if (i < a.n) {
-      double rec[kNRec];
-      const uint32_t info = init_sat(a, g, i, rec, ldeep[threadIdx.x], blockIdx.y == 0);
-#pragma unroll
-      for (int k = 0; k < kNRec; ++k) lrec[k][threadIdx.x] = rec[k];
-      linfo[threadIdx.x] = info;
+  bool deep;
+  {
+    double rec[kNRec], el[7], epoch;
+    const uint32_t info = init_sat(a, g, i, rec, el, &epoch);
+    deep = (info & kInfoDeep) != 0;
+    if (!deep) {
+      put_flags(a, i, info, false);
+      const SatC<TS, TP> c = sat_of<TS, TP>(rec, info, nullptr);
+      PointState<TP> s;
+      const uint32_t code = sgp4_point<TS, TP>(c, g, a.t[0], s);
+      out.put(i, code, s);
     }
   }
-  __syncthreads();
-  const uint32_t q = threadIdx.x;
-  const uint32_t sl = q / a.tt;
-  const int64_t i = i0 + sl;
-  const int64_t j = int64_t(blockIdx.y) * a.tt + (q - sl * a.tt);
-  if (i >= a.n || j >= a.T) return;
-  double x[kNRec];
+  if (deep) fused_deep<TS, TP, kOff32>(a, g, i, 0, 1, out);
+}
+
+// The constants of one satellite as the near-Earth terms of each precision read
+// them (the entries of the record in its order; accessor of load_from).  The
+// sizes are odd multiples of 16 bytes, so that neighbouring satellites' entries
+// lie in different banks.
+template <class TS, class TP>
+struct LdsSat;
+template <>
+struct LdsSat<double, float> {  // as the mixed path: double secular terms, float periodic and drag terms
+  double d[kEpochMin + 1];
+  float f[kNRec - kEta];
+  uint32_t info;
+  __device__ __forceinline__ void put(const double* rec) {
 #pragma unroll
-  for (int k = 0; k < kNRec; ++k) x[k] = lrec[k][sl];
-  const SatC<TS, TP> c = sat_of<TS, TP>(x, linfo[sl], ldeep[sl]);
-  PointState<TP> s;
-  const uint32_t code = (c.info & kInfoDeep) ? deep_point<TS, TP>(c, g, a.t[j], s) : sgp4_point<TS, TP>(c, g, a.t[j], s);
-  // kOff32: every point index is below 2^30 and fits 32-bit arithmetic
-  out.put(kOff32 ? int64_t(uint32_t(i) * uint32_t(a.T) + uint32_t(j)) : i * a.T + j, code, s);
+    for (int k = 0; k <= kEpochMin; ++k) d[k] = rec[k];
+#pragma unroll
+    for (int k = kEta; k < kNRec; ++k) f[k - kEta] = float(rec[k]);
+  }
+  __device__ __forceinline__ double dbl(int k) const { return k <= kEpochMin ? d[k] : 0.0; }
+  __device__ __forceinline__ float flt(int k) const { return k >= kEta ? f[k - kEta] : 0.0f; }
+};
+template <>
+struct LdsSat<double, double> {  // all but the folded short-period coefficients
+  double d[kNRec - 6];
+  uint32_t info;
+  uint32_t pad[7];
+  __device__ __forceinline__ void put(const double* rec) {
+#pragma unroll
+    for (int k = 0; k < kNRec; ++k)
+      if (k < kSpA1 || k > kSpCI) d[k < kSpA1 ? k : k - 6] = rec[k];
+  }
+  __device__ __forceinline__ double dbl(int k) const { return k < kSpA1 ? d[k] : k > kSpCI ? d[k - 6] : 0.0; }
+  __device__ __forceinline__ float flt(int) const { return 0.0f; }
+};
+template <>
+struct LdsSat<float, float> {  // floats, the epoch in double
+  double epoch;
+  float f[kNRec];
+  uint32_t info;
+  __device__ __forceinline__ void put(const double* rec) {
+    epoch = rec[kEpochMin];
+#pragma unroll
+    for (int k = 0; k < kNRec; ++k) f[k] = float(rec[k]);
+  }
+  __device__ __forceinline__ double dbl(int) const { return epoch; }
+  __device__ __forceinline__ float flt(int k) const { return f[k]; }
+};
+static_assert(sizeof(LdsSat<double, float>) == 13 * 16 && sizeof(LdsSat<double, double>) == 19 * 16 &&
+                  sizeof(LdsSat<float, float>) == 11 * 16,
+              "odd multiples of 16 bytes");
+static_assert(kSpCI == kSpA1 + 5, "six folded coefficients");
+#define SGP4MI_LDS_REC(TS, TP)                                                                                 \
+  template <> __device__ __forceinline__ double rec_val<double, const LdsSat<TS, TP>*>(const LdsSat<TS, TP>* s, int k) { \
+    return s->dbl(k);                                                                                          \
+  }                                                                                                            \
+  template <> __device__ __forceinline__ float rec_val<float, const LdsSat<TS, TP>*>(const LdsSat<TS, TP>* s, int k) {   \
+    return s->flt(k);                                                                                          \
+  }
+SGP4MI_LDS_REC(double, float)
+SGP4MI_LDS_REC(double, double)
+SGP4MI_LDS_REC(float, float)
+#undef SGP4MI_LDS_REC
+
+// kFusedSats satellites, times [y per, (y + 1) per) of the list.  Bound by VALU
+// issue.  One wavefront of sixteen initialising for 64 satellites, in runs of 16
+// times, took 204 us at 300,007 x 19 mixed, this 62; a lane per satellite walking
+// its times in registers, outputs regrouped through LDS by eight times, 107
+// (pieces of cache lines); 1M x 8 FP64 242 -> 185, 300,000 x 2 mixed 33 -> 17.
+template <class TS, class TP, bool kOff32>
+__global__ void __launch_bounds__(kFusedBlock) __attribute__((amdgpu_waves_per_eu(4)))
+    fused_kernel(FusedArgs a, Out<TP, kOff32> out) {
+  __shared__ __align__(16) LdsSat<TS, TP> sats[kFusedSats];
+  const int64_t i0 = int64_t(blockIdx.x) * kFusedSats;
+  const int32_t ns = int32_t(a.n - i0 < kFusedSats ? a.n - i0 : kFusedSats);
+  const Grav g = grav_of(a);
+  bool deep = false;
+  if (int32_t(threadIdx.x) < ns) {
+    double rec[kNRec], el[7], epoch;
+    const uint32_t info = init_sat(a, g, i0 + threadIdx.x, rec, el, &epoch);
+    deep = (info & kInfoDeep) != 0;
+    if (!deep) put_flags(a, i0 + threadIdx.x, info, false);
+    sats[threadIdx.x].put(rec);
+    sats[threadIdx.x].info = info;
+  }
+  __syncthreads();
+  const int64_t t0 = int64_t(blockIdx.y) * a.per;
+  const int32_t nt = int32_t(t0 + a.per < a.T ? a.per : a.T - t0);
+  const int32_t step_s = kFusedBlock / nt, step_j = kFusedBlock - step_s * nt;  // one pass further: satellites, times
+  int32_t s = int32_t(threadIdx.x) / nt, j = int32_t(threadIdx.x) - s * nt;
+  while (s < ns) {
+    const LdsSat<TS, TP>* const p = &sats[s];
+    asm volatile("" ::: "memory");
+    SatC<TS, TP> c = load_from<TS, TP, const LdsSat<TS, TP>*, const LdsSat<TS, TP>*>(p, p);
+    if (!(c.info & kInfoDeep)) {
+      PointState<TP> st;
+      const uint32_t code = sgp4_point<TS, TP>(c, g, a.t[t0 + j], st);
+      // kOff32: every point index is below 2^30 and fits 32-bit arithmetic
+      out.put(kOff32 ? int64_t(uint32_t(i0 + s) * uint32_t(a.T) + uint32_t(t0 + j)) : (i0 + s) * a.T + t0 + j, code, st);
+    }
+    s += step_s;
+    j += step_j;
+    if (j >= nt) {
+      j -= nt;
+      ++s;
+    }
+  }
+  if (deep) fused_deep<TS, TP, kOff32>(a, g, i0 + threadIdx.x, t0, t0 + nt, out);
 }
 
 template <class TP>
@@ -155,13 +264,12 @@ template <class TS, class TP, bool kOff32>
 static void fused_go(const FusedArgs& a, void* r, void* v, uint8_t* err, hipStream_t s) {
   const int64_t P = a.n * a.T;
   Out<TP, kOff32> o{static_cast<TP*>(r), static_cast<TP*>(v), err, P};
-  const unsigned gx = unsigned((a.n + 63) / 64);
   if (a.T == 1) {
-    hipLaunchKernelGGL((fused_one_kernel<TS, TP, kOff32>), dim3(gx), dim3(64), 0, s, a, o);
+    hipLaunchKernelGGL((fused_one_kernel<TS, TP, kOff32>), dim3(unsigned((a.n + 63) / 64)), dim3(64), 0, s, a, o);
     return;
   }
-  const unsigned gy = unsigned((a.T + a.tt - 1) / a.tt);
-  hipLaunchKernelGGL((fused_kernel<TS, TP, kOff32>), dim3(gx, gy), dim3(64 * a.tt), 0, s, a, o);
+  const dim3 grid(unsigned((a.n + kFusedSats - 1) / kFusedSats), unsigned((a.T + a.per - 1) / a.per));
+  hipLaunchKernelGGL((fused_kernel<TS, TP, kOff32>), grid, dim3(kFusedBlock), 0, s, a, o);
 }
 
 template <class TS, class TP>
@@ -170,11 +278,10 @@ static void fused_t(const FusedArgs& a, void* r, void* v, uint8_t* err, hipStrea
   else fused_go<TS, TP, false>(a, r, v, err, s);
 }
 
-// Largest T the fused grid covers (ceil(T / tt) workgroups in y).
+// Largest T and n of a fused launch, as the interface states them (the grid
+// itself is smaller: 64 lanes per 64 satellites in x, at most 4,096 groups of
+// times in y).
 int64_t fused_max_T() { return int64_t(65535) * kFusedTT; }
-
-// Whether the fused grid's x extent (ceil(n / 64) workgroups of 64 tt lanes)
-// fits a dispatch's 2^32 work-items.
 bool fused_fits(int64_t n, int64_t T) {
   const uint64_t tt = uint64_t(T < kFusedTT ? T : kFusedTT);
   return grid_fits(uint64_t((n + 63) / 64), 64 * (tt > 0 ? tt : 1));
@@ -189,9 +296,12 @@ hipError_t launch_fused(int precision, const double g[5], double ref_day, int64_
   a.elem = elem;
   a.t = t;
   a.user_flags = user_flags;
-  a.mu = g[0]; a.radius = g[1]; a.j2 = g[2]; a.j3 = g[3]; a.j4 = g[4];
+  a.grav = grav_in(g);
+  a.vkms = a.grav.radius * a.grav.ke / 60.0;
   a.ref_day = ref_day;
-  a.tt = uint32_t(T < kFusedTT ? T : kFusedTT);
+  // enough workgroups to fill the chip, as far as there are times
+  const int64_t wgs = (n + kFusedSats - 1) / kFusedSats, groups = std::min<int64_t>(T, (1024 + wgs - 1) / wgs);
+  a.per = (T + groups - 1) / groups;
   switch (precision) {
     case 0: fused_t<double, double>(a, r, v, err, s); break;
     case 1: fused_t<float, float>(a, r, v, err, s); break;

@@ -16,7 +16,8 @@ struct InitArgs {
   Slot* slots;
   DeepSlot* deep;
   uint8_t* user_flags;  // nullable
-  double mu, radius, j2, j3, j4;
+  GravIn grav;
+  double mu, vkms;
   double ref_day;       // reference instant of the epoch row, days after JD 2415020.0
   double gen;           // this initialisation's generation number (kHGen)
 };
@@ -29,27 +30,25 @@ template <bool kStaged>
 __global__ void __launch_bounds__(64) init_kernel(InitArgs a) {
   __shared__ Slot stage[kStaged ? 64 : 1];
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  const double ke = 60.0 / sqrt(a.radius * a.radius * a.radius / a.mu);
-  const double j3oj2 = (a.j3 == 0.0) ? 0.0 : a.j3 / a.j2;
   if (i == 0) {
     double* h = a.hdr;
     h[kHMagic] = kMagic;
     h[kHN] = double(a.n);
     h[kHNpad] = double(a.npad);
-    h[kHKe] = ke;
-    h[kHRadius] = a.radius;
-    h[kHVkms] = a.radius * ke / 60.0;
-    h[kHK2] = 0.5 * a.j2;
-    h[kHJ2] = a.j2;
-    h[kHJ3oJ2] = j3oj2;
-    h[kHJ4] = a.j4;
+    h[kHKe] = a.grav.ke;
+    h[kHRadius] = a.grav.radius;
+    h[kHVkms] = a.vkms;
+    h[kHK2] = 0.5 * a.grav.j2;
+    h[kHJ2] = a.grav.j2;
+    h[kHJ3oJ2] = a.grav.j3oj2;
+    h[kHJ4] = a.grav.j4;
     h[kHMu] = a.mu;
     h[kHRefDay] = a.ref_day;
     h[kHGen] = a.gen;
     float* hf = reinterpret_cast<float*>(h + kHF32);
-    hf[0] = float(a.radius);
-    hf[1] = float(a.radius * ke / 60.0);
-    hf[2] = float(0.5 * a.j2);
+    hf[0] = float(a.grav.radius);
+    hf[1] = float(a.vkms);
+    hf[2] = float(0.5 * a.grav.j2);
     hf[3] = 0.0f;
   }
   const int64_t n = a.n;
@@ -60,15 +59,14 @@ __global__ void __launch_bounds__(64) init_kernel(InitArgs a) {
 #pragma unroll
     for (int k = 0; k < 7; ++k) el[k] = a.elem[k * n + i];
     const double epoch = a.elem[7 * n + i];
-    GravIn gi{a.radius, a.j2, a.j4, ke, j3oj2};
     double rec[kNRec];
     uint32_t code;
     bool isimp, deep;
-    init_record<double>(gi, el, rec, &code, &isimp, &deep);
+    init_record<double>(a.grav, el, rec, &code, &isimp, &deep);
     bool resonant = false;
     if (deep && code == 0) {
       double d[kNDeep];
-      init_deep(el, rec, ke, a.ref_day + epoch, d);
+      init_deep(el, rec, a.grav.ke, a.ref_day + epoch, d);
       resonant = d[kDRes] != 0.0;
 #pragma unroll
       for (int k = 0; k < kNDeep; ++k) a.deep[i].d[k] = d[k];
@@ -128,7 +126,9 @@ hipError_t launch_init(const double g[5], double ref_day, int64_t n, const doubl
   a.ref_day = ref_day;
   a.gen = next_generation();
   a.user_flags = user_flags;
-  a.mu = g[0]; a.radius = g[1]; a.j2 = g[2]; a.j3 = g[3]; a.j4 = g[4];
+  a.grav = grav_in(g);
+  a.mu = g[0];
+  a.vkms = a.grav.radius * a.grav.ke / 60.0;
   const int64_t blocks = (n + 63) / 64;  // 64-wide: a short kernel spread over more compute units
   if (n >= kInitStagedFrom)
     hipLaunchKernelGGL(init_kernel<true>, dim3(unsigned(blocks)), dim3(64), 0, s, a);

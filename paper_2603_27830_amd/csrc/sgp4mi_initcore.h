@@ -12,6 +12,8 @@
 // boundary of section 6) are resolved here, once per satellite.
 #pragma once
 
+#include <cmath>
+
 #include "sgp4mi_common.h"
 #include "sgp4mi_math.h"
 
@@ -47,14 +49,6 @@ __device__ __forceinline__ Dual1 operator/(double a, Dual1 b) {
   const double q = a / b.v;
   return Dual1(q, -q * b.d / b.v);
 }
-__device__ __forceinline__ Dual1 sqrt(Dual1 x) {
-  const double s = ::sqrt(x.v);
-  return Dual1(s, 0.5 * x.d / s);
-}
-__device__ __forceinline__ Dual1 cbrt(Dual1 x) {
-  const double c = ::cbrt(x.v);
-  return Dual1(c, x.d / (3.0 * c * c));
-}
 __device__ __forceinline__ Dual1 fabs(Dual1 x) { return x.v < 0 ? -x : x; }
 __device__ __forceinline__ void sin_cos(Dual1 x, Dual1* s, Dual1* c) {
   double sv, cv;
@@ -71,21 +65,58 @@ using dual::value;
 // propagation kernels (any argument, no quadrant logic, no library branches).
 __device__ __forceinline__ void sin_cos(double x, double* s, double* c) { sincos_rr(x, s, c); }
 using dual::sin_cos;
-// Quotient: the reciprocal estimate refined by Newton steps times the
-// numerator (within about an ulp of the rounded quotient, and a shorter
-// dependency chain than the correctly rounded division); for dual numbers the
-// same, one reciprocal for the value and the derivative.
-__device__ __forceinline__ double quot(double a, double b) { return a * rcp(b); }
-template <class A, class B>
-__device__ __forceinline__ Dual1 quot(A a, B b) {
-  const Dual1 x(a), y(b);
-  const double r = rcp(y.v), q = x.v * r;
-  return Dual1(q, (x.d - q * y.d) * r);
+// Reciprocal and reciprocal square root: the hardware estimate refined by two
+// Newton steps (within about an ulp, and a shorter chain than the correctly
+// rounded division and root), and x^(-2/3), the semi-major axis of a mean
+// motion: a float estimate of x^(-1/3) (relative error below 2^-21) and one
+// third-order step y (1 + e / 3 + 2 e^2 / 9), e = 1 - x y^3.  Arguments beyond
+// float's comfortable range take the library's cube root.  For dual numbers the
+// derivatives follow from the values.
+__device__ __forceinline__ double recip(double x) { return rcp(x); }
+__device__ __forceinline__ double rsqrt_nr(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+  const double h = 0.5 * x;
+  y = fma(y, fma(-h * y, y, 0.5), y);
+  return fma(y, fma(-h * y, y, 0.5), y);
+}
+__device__ __forceinline__ double pow_m23(double x) {
+  if (!(x > 1.0e-30 && x < 1.0e30)) {
+    const double c = ::cbrt(1.0 / x);
+    return c * c;
+  }
+  const double y = double(__builtin_amdgcn_exp2f(-0.33333333333f * __builtin_amdgcn_logf(float(x))));
+  const double e = fma(-x * y, y * y, 1.0);
+  const double z = y * fma(e, fma(e, 2.0 / 9.0, 1.0 / 3.0), 1.0);
+  return z * z;
+}
+__device__ __forceinline__ Dual1 recip(Dual1 x) {
+  const double r = rcp(x.v);
+  return Dual1(r, -r * r * x.d);
+}
+__device__ __forceinline__ Dual1 rsqrt_nr(Dual1 x) {
+  const double y = rsqrt_nr(x.v);
+  return Dual1(y, -0.5 * y * y * y * x.d);
+}
+__device__ __forceinline__ Dual1 pow_m23(Dual1 x) {
+  const double a = pow_m23(x.v);
+  return Dual1(a, -(2.0 / 3.0) * a * rcp(x.v) * x.d);
 }
 
+// Gravity model and the lengths of the drag model in earth radii (s = 1 + 78 km,
+// q0 - s = 42 km, the 220 km perigee of the simplified drag), uniform over a
+// launch.
 struct GravIn {
   double radius, j2, j4, ke, j3oj2;
+  double inv_ke, inv_radius, s78, q42, p220;
 };
+__host__ __device__ __forceinline__ GravIn grav_in(double radius, double j2, double j4, double ke, double j3oj2) {
+  return GravIn{radius, j2, j4, ke, j3oj2, 1.0 / ke, 1.0 / radius, 1.0 + 78.0 / radius, 42.0 / radius,
+                1.0 + 220.0 / radius};
+}
+// ke (er^1.5 / min) and J3 / J2 of {mu, R, J2, J3, J4}.
+inline GravIn grav_in(const double g[5]) {
+  return grav_in(g[1], g[2], g[4], 60.0 / std::sqrt(g[1] * g[1] * g[1] / g[0]), g[3] == 0.0 ? 0.0 : g[3] / g[2]);
+}
 
 // el: n0 (Kozai, rad/min), e0, i0, node0, argp0, M0, bstar.  Writes the
 // record entries (all but kEpochMin), the satellite code and the flags
@@ -94,9 +125,7 @@ struct GravIn {
 template <class S>
 __device__ __forceinline__ void init_record(const GravIn& g, const S el[7], S rec[kNRec], uint32_t* code_out,
                                             bool* isimp_out, bool* deep_out) {
-  using ::cbrt;
   using ::fabs;
-  using ::sqrt;
   const S& no_kozai = el[0];
   const S& ecco = el[1];
   const S& inclo = el[2];
@@ -104,38 +133,42 @@ __device__ __forceinline__ void init_record(const GravIn& g, const S el[7], S re
   const S& argpo = el[4];
   const S& mo = el[5];
   const S& bstar = el[6];
-  const double R = g.radius, J2 = g.j2, J4 = g.j4, ke = g.ke, j3oj2 = g.j3oj2;
+  const double R = g.radius, J2 = g.j2, J4 = g.j4, j3oj2 = g.j3oj2;
 
   S sin_i, cos_i;
   sin_cos(inclo, &sin_i, &cos_i);
   const S c2 = cos_i * cos_i;
   const S omeosq = 1.0 - ecco * ecco;  // beta0^2
-  const S rteosq = sqrt(omeosq);       // beta0
+  const S irt = rsqrt_nr(omeosq);      // 1 / beta0
+  const S iom = irt * irt;             // 1 / beta0^2
+  const S rteosq = omeosq * irt;
   const S con41 = 3.0 * c2 - 1.0;
   const S x1mth2 = 1.0 - c2;
   const S x7thm1 = 7.0 * c2 - 1.0;
 
   // Original mean motion: invert the Kozai definition with the second-order
   // correction of the published model.
-  const S ak = cbrt(quot(ke, no_kozai));
-  const S a1 = ak * ak;
-  const S d1 = quot(0.75 * J2 * con41, rteosq * omeosq);
-  const S del1 = quot(d1, a1 * a1);
-  const S adel = a1 * (1.0 - del1 * (1.0 / 3.0 + del1 * (1.0 + (134.0 / 81.0) * del1)));
-  const S del0 = quot(d1, adel * adel);
-  const S nbar = quot(no_kozai, 1.0 + del0);
-  const S ab = cbrt(quot(ke, nbar));
-  const S abar = ab * ab;
+  const S a1 = pow_m23(fabs(no_kozai) * g.inv_ke);
+  const S d1 = (0.75 * J2) * con41 * (irt * iom);
+  const S ia1 = recip(a1);
+  const S del1 = d1 * (ia1 * ia1);
+  // 1 / adel = (1 / a1) / (the series)
+  const S ser = 1.0 - del1 * (1.0 / 3.0 + del1 * (1.0 + (134.0 / 81.0) * del1));
+  const S iadel = ia1 * recip(ser);
+  const S del0 = d1 * (iadel * iadel);
+  const S nbar = no_kozai * recip(1.0 + del0);
+  const S abar = pow_m23(fabs(nbar) * g.inv_ke);
+  const S iab = recip(abar);
 
   // Perigee height -> density parameter s and (q0 - s)^4.
   const S perigee_er = abar * (1.0 - ecco);
   const S perigee_km = (perigee_er - 1.0) * R;
-  S sfour = S(1.0 + 78.0 / R);
-  S qoms = S((120.0 - 78.0) / R);
+  S sfour = S(g.s78);
+  S qoms = S(g.q42);
   if (value(perigee_km) < 156.0) {
     const S s_km = (value(perigee_km) < 98.0) ? S(20.0) : perigee_km - 78.0;
-    qoms = (120.0 - s_km) / R;
-    sfour = 1.0 + s_km / R;
+    qoms = (120.0 - s_km) * g.inv_radius;
+    sfour = 1.0 + s_km * g.inv_radius;
   }
   const S qoms2 = qoms * qoms;
   const S qoms24 = qoms2 * qoms2;
@@ -144,35 +177,39 @@ __device__ __forceinline__ void init_record(const GravIn& g, const S el[7], S re
   bool deep = false;
   if (!(value(ecco) >= 0.0 && value(ecco) < 1.0)) code = 1;
   else if (!(value(nbar) > 0.0)) code = 2;
-  else if (kTwoPi / value(nbar) >= 225.0) deep = true;
-  const bool isimp = deep || value(perigee_er) < 1.0 + 220.0 / R;
+  else if (value(nbar) <= kTwoPi / 225.0) deep = true;  // a period of 225 minutes or more
+  const bool isimp = deep || value(perigee_er) < g.p220;
 
   // Power-law drag coefficients.
-  const S tsi = quot(1.0, abar - sfour);
+  const S above = abar - sfour;
+  const S tsi = recip(above);
   const S eta = abar * ecco * tsi;
   const S etasq = eta * eta;
   const S eeta = ecco * eta;
   const S psisq = fabs(1.0 - etasq);
   const S tsi2 = tsi * tsi;
   const S coef = qoms24 * tsi2 * tsi2;
-  const S coef1 = quot(coef, psisq * psisq * psisq * sqrt(psisq));
+  const S ips = rsqrt_nr(psisq), ips2 = ips * ips;  // psisq^-1/2, 1 / psisq
+  const S coef1 = coef * (ips2 * ips2) * (ips2 * ips);
   const S cc2 = coef1 * nbar *
                 (abar * (1.0 + 1.5 * etasq + eeta * (4.0 + etasq)) +
-                 0.375 * J2 * quot(tsi, psisq) * con41 * (8.0 + 3.0 * etasq * (8.0 + etasq)));
+                 0.375 * J2 * (tsi * ips2) * con41 * (8.0 + 3.0 * etasq * (8.0 + etasq)));
   const S cc1 = bstar * cc2;
-  const S cc3 = (value(ecco) > 1.0e-4) ? quot(-2.0 * coef * tsi * j3oj2 * nbar * sin_i, ecco) : S(0.0);
+  const bool round = !(value(ecco) > 1.0e-4);
+  const S ie = recip(ecco);
+  const S cc3 = round ? S(0.0) : -2.0 * coef * tsi * j3oj2 * nbar * sin_i * ie;
   S sin_w, cos_w;
   sin_cos(argpo, &sin_w, &cos_w);
   const S cos_2w = 2.0 * cos_w * cos_w - 1.0;
   const S cc4 = 2.0 * nbar * coef1 * abar * omeosq *
                 (eta * (2.0 + 0.5 * etasq) + ecco * (0.5 + 2.0 * etasq) -
-                 quot(J2 * tsi, abar * psisq) *
+                 (J2 * tsi) * (iab * ips2) *
                      (-3.0 * con41 * (1.0 - 2.0 * eeta + etasq * (1.5 - 0.5 * eeta)) +
                       0.75 * x1mth2 * (2.0 * etasq - eeta * (1.0 + etasq)) * cos_2w));
   const S cc5 = 2.0 * coef1 * abar * omeosq * (1.0 + 2.75 * (etasq + eeta) + eeta * etasq);
 
   // Secular rates.
-  const S pinv = quot(1.0, abar * omeosq);
+  const S pinv = iab * iom;
   const S pinvsq = pinv * pinv;
   const S c4 = c2 * c2;
   const S temp1 = 1.5 * J2 * pinvsq * nbar;
@@ -187,12 +224,13 @@ __device__ __forceinline__ void init_record(const GravIn& g, const S el[7], S re
   S sin_m0, cos_m0;
   sin_cos(mo, &sin_m0, &cos_m0);
   S argpcof = bstar * cc3 * cos_w;
-  S xmcof = (value(ecco) > 1.0e-4) ? quot(-(2.0 / 3.0) * coef * bstar, eeta) : S(0.0);
+  // 1 / (e eta) with eta = a e / (a - s)
+  S xmcof = round ? S(0.0) : -(2.0 / 3.0) * coef * bstar * (ie * ie) * (iab * above);
   const S nodecf = 3.5 * omeosq * xhdot1 * cc1;
   const S t2cof = 1.5 * cc1;
   S den = 1.0 + cos_i;
   if (::fabs(value(den)) <= 1.5e-12) den = S(1.5e-12);
-  const S xlcof = quot(-0.25 * j3oj2 * sin_i * (3.0 + 5.0 * cos_i), den);
+  const S xlcof = -0.25 * j3oj2 * sin_i * (3.0 + 5.0 * cos_i) * recip(den);
   const S aycof = -0.5 * j3oj2 * sin_i;
   const S dm = 1.0 + eta * cos_m0;
   const S delmo = dm * dm * dm;

@@ -457,7 +457,7 @@ __global__ void __launch_bounds__(kVjpBlock, kVjpBlocksPerCU<double>)
     if ((info & (kInfoCodeMask | kInfoDeep)) == 0) {
       Dual1 el[7];
       for (int k = 0; k < 7; ++k) el[k] = Dual1(elem[k * n + i], k == m ? 1.0 : 0.0);
-      GravIn gi{rv.hdr[kHRadius], rv.hdr[kHJ2], rv.hdr[kHJ4], rv.hdr[kHKe], rv.hdr[kHJ3oJ2]};
+      const GravIn gi = grav_in(rv.hdr[kHRadius], rv.hdr[kHJ2], rv.hdr[kHJ4], rv.hdr[kHKe], rv.hdr[kHJ3oJ2]);
       Dual1 rec[kNRec];
       uint32_t code;
       bool isimp, dsp;
@@ -535,8 +535,7 @@ __device__ __forceinline__ void vjp_sat(const RecordView& rv, int64_t n, const d
     if ((c.info & (kInfoCodeMask | kInfoDeep)) == 0) {
       Dual1 el[7];
       for (int k = 0; k < 7; ++k) el[k] = Dual1(elem[k * n + i], k == m ? 1.0 : 0.0);
-      const double R = rv.hdr[kHRadius];
-      GravIn gi{R, rv.hdr[kHJ2], rv.hdr[kHJ4], rv.hdr[kHKe], rv.hdr[kHJ3oJ2]};
+      const GravIn gi = grav_in(rv.hdr[kHRadius], rv.hdr[kHJ2], rv.hdr[kHJ4], rv.hdr[kHKe], rv.hdr[kHJ3oJ2]);
       Dual1 rec[kNRec];
       uint32_t code;
       bool isimp, dsp;
@@ -955,7 +954,7 @@ __device__ __forceinline__ void jac_sat(const RecordView& rv, int64_t n, const d
     if (scode == 0) {
       Dual1 el[7];
       for (int k = 0; k < 7; ++k) el[k] = Dual1(elem[k * n + i], k == m ? 1.0 : 0.0);
-      GravIn gi{rv.hdr[kHRadius], rv.hdr[kHJ2], rv.hdr[kHJ4], rv.hdr[kHKe], rv.hdr[kHJ3oJ2]};
+      const GravIn gi = grav_in(rv.hdr[kHRadius], rv.hdr[kHJ2], rv.hdr[kHJ4], rv.hdr[kHKe], rv.hdr[kHJ3oJ2]);
       Dual1 rec[kNRec];
       uint32_t code;
       bool isimp, dsp;
@@ -1011,7 +1010,7 @@ __global__ void __launch_bounds__(kVjpBlock, kJacBlocksPerCU<double>)
     if (s < ns && (rv.slots[sat0 + s].info & (kInfoCodeMask | kInfoDeep)) == 0) {
       Dual1 el[7];
       for (int k = 0; k < 7; ++k) el[k] = Dual1(elem[k * n + sat0 + s], k == m ? 1.0 : 0.0);
-      GravIn gi{rv.hdr[kHRadius], rv.hdr[kHJ2], rv.hdr[kHJ4], rv.hdr[kHKe], rv.hdr[kHJ3oJ2]};
+      const GravIn gi = grav_in(rv.hdr[kHRadius], rv.hdr[kHJ2], rv.hdr[kHJ4], rv.hdr[kHKe], rv.hdr[kHJ3oJ2]);
       Dual1 rec[kNRec];
       uint32_t code;
       bool isimp, dsp;
