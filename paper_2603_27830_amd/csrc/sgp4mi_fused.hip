@@ -168,16 +168,16 @@ struct LdsSat<double, float> {  // as the mixed path: double secular terms, floa
   __device__ __forceinline__ float flt(int k) const { return k >= kEta ? f[k - kEta] : 0.0f; }
 };
 template <>
-struct LdsSat<double, double> {  // all but the folded short-period coefficients
-  double d[kNRec - 6];
+struct LdsSat<double, double> {  // all but the unfolded inclination functions
+  double d[kNRec - 3];
   uint32_t info;
-  uint32_t pad[7];
+  uint32_t pad;
   __device__ __forceinline__ void put(const double* rec) {
 #pragma unroll
     for (int k = 0; k < kNRec; ++k)
-      if (k < kSpA1 || k > kSpCI) d[k < kSpA1 ? k : k - 6] = rec[k];
+      if (k < kC41 || k > kX7) d[k < kC41 ? k : k - 3] = rec[k];
   }
-  __device__ __forceinline__ double dbl(int k) const { return k < kSpA1 ? d[k] : k > kSpCI ? d[k - 6] : 0.0; }
+  __device__ __forceinline__ double dbl(int k) const { return k < kC41 ? d[k] : k > kX7 ? d[k - 3] : 0.0; }
   __device__ __forceinline__ float flt(int) const { return 0.0f; }
 };
 template <>
@@ -196,7 +196,7 @@ struct LdsSat<float, float> {  // floats, the epoch in double
 static_assert(sizeof(LdsSat<double, float>) == 13 * 16 && sizeof(LdsSat<double, double>) == 19 * 16 &&
                   sizeof(LdsSat<float, float>) == 11 * 16,
               "odd multiples of 16 bytes");
-static_assert(kSpCI == kSpA1 + 5, "six folded coefficients");
+static_assert(kX7 == kC41 + 2, "three unfolded functions");
 #define SGP4MI_LDS_REC(TS, TP)                                                                                 \
   template <> __device__ __forceinline__ double rec_val<double, const LdsSat<TS, TP>*>(const LdsSat<TS, TP>* s, int k) { \
     return s->dbl(k);                                                                                          \

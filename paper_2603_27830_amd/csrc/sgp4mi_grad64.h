@@ -43,14 +43,6 @@ __device__ __forceinline__ void grad64_extras(double* c, double j3oj2) {
   c[kAycofI] = -0.5 * j3oj2 * ci;
 }
 
-// 1 / sqrt(x) for positive x: the hardware estimate and two Newton steps.
-__device__ __forceinline__ double rsqrt_pos(double x) {
-  double y = __builtin_amdgcn_rsq(x);
-  const double h = 0.5 * x;
-  y = fma(y, fma(-h * y, y, 0.5), y);
-  return fma(y, fma(-h * y, y, 0.5), y);
-}
-
 // What the derivatives need of a point's forward pass.
 struct Point64 {
   // secular
@@ -75,13 +67,15 @@ struct Point64 {
 __device__ __forceinline__ uint32_t point64_secular(const double* c, double t_abs, Point64& p, double* U) {
   const double t = t_abs - c[kEpochMin];
   p.t = t;
-  const double Mdf = fma(c[kMdot], t, c[kM0]);
+  double Mdf = fma(c[kMdot], t, c[kM0]);
+  if (fabs(t) > kFarMin) Mdf = wrap_pi(Mdf);
   sincos_rr(Mdf, &p.sMdf, &p.cMdf);
   p.x = fma(c[kEta], p.cMdf, 1.0);
   p.x3 = p.x * p.x * p.x - c[kDM0];
   const double dMa = fma(c[kMcof], p.x3, c[kArgpcof] * t);
   double M = Mdf + dMa;
-  const double argp = fma(c[kArgpdot], t, c[kArgp0]) - dMa;
+  double argp = fma(c[kArgpdot], t, c[kArgp0]) - dMa;
+  if (fabs(t) > kFarMin) argp = wrap_pi(argp);
   double sM = p.sMdf;
   p.cM = p.cMdf;
   if (fabs(dMa) > kRotMax) sincos_rr(M, &sM, &p.cM);
@@ -97,7 +91,7 @@ __device__ __forceinline__ uint32_t point64_secular(const double* c, double t_ab
   e = fmax(e, 1.0e-6);
   p.e = e;
   sincos_rr(argp, &p.sw, &p.cw);
-  const double ra = rsqrt_pos(a);
+  const double ra = rsq(a);
   p.ia = ra * ra;
   const double ax = e * p.cw;
   p.om0 = fma(-e, e, 1.0);
@@ -114,32 +108,20 @@ __device__ __forceinline__ uint32_t point64_secular(const double* c, double t_ab
 __device__ __forceinline__ uint32_t point64_orbit(const double* c, const Grav& g, double t, double U, Point64& p) {
   const double a = p.a, ax = p.ax, ay = p.ay, ra = p.ra;
   double sp, cp;
-  sincos_rr(U, &sp, &cp);
-  {
-    double dpsi = 0.0;
-    const KeplerExit<double> done(fabs(ax) + fabs(ay));
-    for (int k = 0; k < 10; ++k) {
-      double step = (ax * sp - ay * cp - dpsi) * rcp(1.0 - ax * cp - ay * sp);
-      step = clamp_step(step);
-      dpsi = dpsi + step;
-      if (fabs(step) <= kRotMax) rotate_small(&sp, &cp, step);
-      else sincos_rr(U + dpsi, &sp, &cp);
-      if (__all(done(fabs(step)))) break;
-    }
-  }
+  const double iD0 = kepler64(U, ax, ay, &sp, &cp);
   p.sp = sp;
   p.cp = cp;
   p.ecE = ax * cp + ay * sp;
   p.esE = ax * sp - ay * cp;
   const double D = 1.0 - p.ecE;
-  p.iD = rcp(D);
+  p.iD = rcp_from(D, iD0);
   p.om = 1.0 - (ax * ax + ay * ay);
   if (!(a * p.om >= 0.0)) return 4;
   p.rl = a * D;
   p.irl = p.ia * p.iD;
   p.sr = ra * p.iD;  // sqrt(a) / r_l
   p.rdotl = p.sr * p.esE;
-  p.ibeta = rsqrt_pos(p.om);
+  p.ibeta = rsq(p.om);
   p.betal = p.om * p.ibeta;
   p.rvdotl = p.sr * p.betal;
   p.iopb = rcp(1.0 + p.betal);
@@ -161,22 +143,13 @@ __device__ __forceinline__ uint32_t point64_orbit(const double* c, const Grav& g
   const double du = -0.25 * p.k2 * c[kX7] * p.s2;
   const double kc = 1.5 * p.k2 * c[kCosi];
   const double dinc = kc * c[kSini] * p.c2;
-  if (fabs(du) <= kRotMax) {
-    // a unit vector up to rounding: one Newton step normalises it
-    const double n2 = p.sinu * p.sinu + p.cosu * p.cosu;
-    double h = 1.5 - 0.5 * n2;
-    if (fabs(n2 - 1.0) > 1.0e-8) h = rsq(n2);
-    p.ssu = p.sinu * h;
-    p.csu = p.cosu * h;
-    rotate_small(&p.ssu, &p.csu, du);
-  } else {
-    sincos_rr(arctan2(p.sinu, p.cosu) + du, &p.ssu, &p.csu);
-  }
+  p.ssu = p.sinu;
+  p.csu = p.cosu;
   p.sinc = c[kSini];
   p.cinc = c[kCosi];
-  if (fabs(dinc) <= kRotMax) rotate_small(&p.sinc, &p.cinc, dinc);
-  else sincos_rr(c[kI0] + dinc, &p.sinc, &p.cinc);
-  const double node = fma(t, fma(t, c[kNodecf], c[kNodedot]), c[kNode0]);
+  rotate_node64(&p.ssu, &p.csu, du, &p.sinc, &p.cinc, dinc, c[kI0]);
+  double node = fma(t, fma(t, c[kNodecf], c[kNodedot]), c[kNode0]);
+  if (fabs(t) > kFarMin) node = wrap_pi(node);
   sincos_rr(node + kc * p.s2, &p.snod, &p.cnod);
   return p.mrt < 1.0 ? 6u : 0u;
 }

@@ -22,6 +22,8 @@ namespace sgp4mi {
 // Forward-mode dual number with one tangent (value, derivative).  Kept in its
 // own namespace so its math overloads are found by argument-dependent lookup
 // only and never hide the double versions.
+// An angle whose size sincos_rr takes.
+__device__ __forceinline__ double reduced(double x) { return ::fabs(x) > 1.0e12 ? wrap_pi(x) : x; }
 namespace dual {
 struct Dual1 {
   double v, d;
@@ -52,7 +54,7 @@ __device__ __forceinline__ Dual1 operator/(double a, Dual1 b) {
 __device__ __forceinline__ Dual1 fabs(Dual1 x) { return x.v < 0 ? -x : x; }
 __device__ __forceinline__ void sin_cos(Dual1 x, Dual1* s, Dual1* c) {
   double sv, cv;
-  sincos_rr(x.v, &sv, &cv);
+  sincos_rr(reduced(x.v), &sv, &cv);
   *s = Dual1(sv, cv * x.d);
   *c = Dual1(cv, -sv * x.d);
 }
@@ -63,38 +65,19 @@ __device__ __forceinline__ double value(double x) { return x; }
 using dual::value;
 // Sine and cosine of an element angle: the reduced-range series of the
 // propagation kernels (any argument, no quadrant logic, no library branches).
-__device__ __forceinline__ void sin_cos(double x, double* s, double* c) { sincos_rr(x, s, c); }
+__device__ __forceinline__ void sin_cos(double x, double* s, double* c) { sincos_rr(reduced(x), s, c); }
 using dual::sin_cos;
-// Reciprocal and reciprocal square root: the hardware estimate refined by two
-// Newton steps (within about an ulp, and a shorter chain than the correctly
-// rounded division and root), and x^(-2/3), the semi-major axis of a mean
-// motion: a float estimate of x^(-1/3) (relative error below 2^-21) and one
-// third-order step y (1 + e / 3 + 2 e^2 / 9), e = 1 - x y^3.  Arguments beyond
-// float's comfortable range take the library's cube root.  For dual numbers the
-// derivatives follow from the values.
+// Reciprocal, reciprocal square root and x^(-2/3) of plain and dual numbers (a
+// shorter chain than the correctly rounded division and root); the derivatives
+// follow from the values.
 __device__ __forceinline__ double recip(double x) { return rcp(x); }
-__device__ __forceinline__ double rsqrt_nr(double x) {
-  double y = __builtin_amdgcn_rsq(x);
-  const double h = 0.5 * x;
-  y = fma(y, fma(-h * y, y, 0.5), y);
-  return fma(y, fma(-h * y, y, 0.5), y);
-}
-__device__ __forceinline__ double pow_m23(double x) {
-  if (!(x > 1.0e-30 && x < 1.0e30)) {
-    const double c = ::cbrt(1.0 / x);
-    return c * c;
-  }
-  const double y = double(__builtin_amdgcn_exp2f(-0.33333333333f * __builtin_amdgcn_logf(float(x))));
-  const double e = fma(-x * y, y * y, 1.0);
-  const double z = y * fma(e, fma(e, 2.0 / 9.0, 1.0 / 3.0), 1.0);
-  return z * z;
-}
+__device__ __forceinline__ double rsqrt_pos(double x) { return rsq(x); }
 __device__ __forceinline__ Dual1 recip(Dual1 x) {
   const double r = rcp(x.v);
   return Dual1(r, -r * r * x.d);
 }
-__device__ __forceinline__ Dual1 rsqrt_nr(Dual1 x) {
-  const double y = rsqrt_nr(x.v);
+__device__ __forceinline__ Dual1 rsqrt_pos(Dual1 x) {
+  const double y = rsq(x.v);
   return Dual1(y, -0.5 * y * y * y * x.d);
 }
 __device__ __forceinline__ Dual1 pow_m23(Dual1 x) {
@@ -139,7 +122,7 @@ __device__ __forceinline__ void init_record(const GravIn& g, const S el[7], S re
   sin_cos(inclo, &sin_i, &cos_i);
   const S c2 = cos_i * cos_i;
   const S omeosq = 1.0 - ecco * ecco;  // beta0^2
-  const S irt = rsqrt_nr(omeosq);      // 1 / beta0
+  const S irt = rsqrt_pos(omeosq);      // 1 / beta0
   const S iom = irt * irt;             // 1 / beta0^2
   const S rteosq = omeosq * irt;
   const S con41 = 3.0 * c2 - 1.0;
@@ -189,7 +172,7 @@ __device__ __forceinline__ void init_record(const GravIn& g, const S el[7], S re
   const S psisq = fabs(1.0 - etasq);
   const S tsi2 = tsi * tsi;
   const S coef = qoms24 * tsi2 * tsi2;
-  const S ips = rsqrt_nr(psisq), ips2 = ips * ips;  // psisq^-1/2, 1 / psisq
+  const S ips = rsqrt_pos(psisq), ips2 = ips * ips;  // psisq^-1/2, 1 / psisq
   const S coef1 = coef * (ips2 * ips2) * (ips2 * ips);
   const S cc2 = coef1 * nbar *
                 (abar * (1.0 + 1.5 * etasq + eeta * (4.0 + etasq)) +

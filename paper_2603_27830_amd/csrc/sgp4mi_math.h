@@ -7,8 +7,8 @@
 // (through h^13 / h^12, truncation below 7e-9) and the double-angle
 // identities sin 2h = 2 sin h cos h, cos 2h = 1 - 2 sin^2 h (no quadrant
 // selection, so nothing depends on k fitting an integer); in double, a table
-// of sin and cos at multiples of pi / 64 and the short series of the
-// remainder (see the function).
+// of sin and cos at multiples of pi / 64, indexed straight from the rounded
+// quotient, and the short series of the remainder (see the function).
 //
 // rotate_small: (sin x, cos x) -> (sin(x+d), cos(x+d)) by angle addition with
 // the series of sin d and cos d; used for |d| <= kRotMax, exact to rounding
@@ -142,25 +142,24 @@ __device__ __forceinline__ double sgpr_const(double x) {
   return x;
 }
 
-// Double: y = x - 2 pi n as above, then y = j pi / 64 + b with |b| <= pi / 128
-// (a two-part pi / 64), the table's sin and cos of j pi / 64 and the series of
-// sin b through b^7 and cos b through b^6 (the next terms are below 4e-19 and
-// 3.3e-18 relative), combined by angle addition.  The table index is clamped,
-// so no input (NaN, infinity, huge) reads outside the table.
+// Double: b = x - n pi / 64 with n the nearest whole number (a two-part pi / 64,
+// the product exact inside the fused multiply-add, |b| <= pi / 128), the table's
+// sin and cos of (n mod 128) pi / 64 and the series of sin b through b^7 and
+// cos b through b^6 (the next terms are below 4e-19 and 3.3e-18 relative),
+// combined by angle addition.  n is rounded by adding 1.5 * 2^52 + 64: the low
+// bits of the sum are n + 64, so the table index takes no conversion, and the
+// mask keeps it inside the table for every input (NaN, infinity, huge).  Angles
+// beyond 1e14, whose spacing exceeds pi / 128, must be reduced before.
 __device__ __forceinline__ void sincos_rr(double x, double* s, double* c) {
-  const double* k = kHalfAngle64;
-  const double n = rint(x * k[20]);
-  double y = fma(-n, k[21], x);
-  y = fma(-n, k[22], y);
-  const double jd = rint(y * 20.371832715762604);  // 64 / pi
-  double b = fma(-jd, 0.04908738521234052, y);     // pi / 64, nearest double
-  b = fma(-jd, 1.9135106236677394e-18, b);         // pi / 64 minus that
-  int j = int(jd) + 64;
-  j = j < 0 ? 0 : (j > 128 ? 128 : j);
-  // The clamped index is non-negative: read the pair at a 32-bit byte offset
-  // from the table's base, seen in the global address space (the load then
-  // takes the base from scalar registers and needs no 64-bit address).
-  uint32_t off = uint32_t(j) * 16u;
+  const double round64 = 6755399441055808.0;       // 1.5 * 2^52 + 64
+  const double m = fma(x, sgpr_const(20.371832715762604), round64);  // 64 / pi
+  const double n = m - round64;
+  double b = fma(-n, sgpr_const(0.04908738521234052), x);  // pi / 64, nearest double
+  b = fma(-n, sgpr_const(1.9135106236677394e-18), b);      // pi / 64 minus that
+  // Read the pair at a 32-bit byte offset from the table's base, seen in the
+  // global address space (the load then takes the base from scalar registers
+  // and needs no 64-bit address).
+  uint32_t off = (uint32_t(__double2loint(m)) & 127u) * 16u;
   asm("" : "+v"(off));
   typedef const __attribute__((address_space(1))) char* GBytes;
   typedef const __attribute__((address_space(1))) double* GDouble;
@@ -179,10 +178,9 @@ __device__ __forceinline__ void sincos_rr(double x, double* s, double* c) {
   }
   p = fma(p, b2, sgpr_const(-1.66666666666666666667e-1));
   const double sb = fma(p * b2, b, b);
-  q = fma(q, b2, -0.5);
-  const double cb = fma(q, b2, 1.0);
-  *s = fma(sa, cb, ca * sb);
-  *c = fma(ca, cb, -(sa * sb));
+  q = fma(q, b2, -0.5) * b2;  // cos b - 1
+  *s = fma(ca, sb, fma(sa, q, sa));
+  *c = fma(-sa, sb, fma(ca, q, ca));
 }
 
 __device__ __forceinline__ void sincos_rr(float x, float* s, float* c) {
@@ -236,14 +234,58 @@ __device__ __forceinline__ void rotate_small(T* s, T* c, T d) {
   *c = c0 * cd - s0 * sd;
 }
 
-// Reciprocal: hardware estimate refined by two Newton steps (double) or the
-// hardware estimate alone (float, about 1 ulp).
-__device__ __forceinline__ double rcp(double x) {
-  double y = __builtin_amdgcn_rcp(x);
-  double e = fma(-x, y, 1.0);
-  y = fma(y, e, y);
-  e = fma(-x, y, 1.0);
-  return fma(y, e, y);
+// Rotations by still smaller angles (double), with fewer terms: |d| <= kRotMid
+// (the sine through d^5, the cosine through d^4; the next terms are below 2e-22
+// and 2e-18) and |d| <= kRotTiny (the sine through d^3; the next is below 3e-17).
+constexpr double kRotMid = 3.2e-3, kRotTiny = 1.25e-3;
+__device__ __forceinline__ void rotate_by(double* s, double* c, double sd, double cd1) {  // sin d, cos d - 1
+  const double s0 = *s, c0 = *c;
+  *s = fma(c0, sd, fma(s0, cd1, s0));
+  *c = fma(-s0, sd, fma(c0, cd1, c0));
+}
+__device__ __forceinline__ void rotate_mid(double* s, double* c, double d) {
+  const double d2 = d * d;
+  double p;
+  {
+#pragma clang fp contract(off)
+    p = d2 * sgpr_const(8.33333333333333333333e-3) + sgpr_const(-1.66666666666666666667e-1);
+  }
+  rotate_by(s, c, fma(p * d2, d, d), d2 * fma(d2, sgpr_const(4.16666666666666666667e-2), -0.5));
+}
+__device__ __forceinline__ void rotate_tiny(double* s, double* c, double d) {
+  const double d2 = d * d;
+  rotate_by(s, c, fma(d2 * sgpr_const(-1.66666666666666666667e-1), d, d),
+            d2 * fma(d2, sgpr_const(4.16666666666666666667e-2), -0.5));
+}
+
+// Reciprocal and reciprocal square root: in double the hardware estimate y
+// (relative error e of 1e-7 or less) and one third-order step, 1 + e + e^2 and
+// 1 + e / 2 + 3 e^2 / 8 (an ulp or so; the root for positive arguments); in
+// float the hardware estimate alone (about 1 ulp).  rcp_from refines an estimate
+// that the caller has (relative error below 1e-5).  x^(-2/3), the semi-major axis
+// of a mean motion: a float estimate of x^(-1/3) (relative error below 2^-21)
+// and one third-order step; arguments beyond float's comfortable range take the
+// library's cube root.
+__device__ __forceinline__ double rcp_from(double x, double y) {
+  const double e = fma(-x, y, 1.0);
+  return fma(y, fma(e, e, e), y);
+}
+__device__ __forceinline__ double rcp(double x) { return rcp_from(x, __builtin_amdgcn_rcp(x)); }
+__device__ __forceinline__ double rsq(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-x * y, y, 1.0);
+  return fma(y * e, fma(e, sgpr_const(0.375), 0.5), y);
+}
+__device__ __forceinline__ float rsq(float x) { return __builtin_amdgcn_rsqf(x); }
+__device__ __forceinline__ double pow_m23(double x) {
+  if (!(x > 1.0e-30 && x < 1.0e30)) {
+    const double c = ::cbrt(1.0 / x);
+    return c * c;
+  }
+  const double y = double(__builtin_amdgcn_exp2f(-0.33333333333f * __builtin_amdgcn_logf(float(x))));
+  const double e = fma(-x * y, y * y, 1.0);
+  const double z = y * fma(e, fma(e, 2.0 / 9.0, 1.0 / 3.0), 1.0);
+  return z * z;
 }
 __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 

@@ -37,39 +37,31 @@ struct Out {
       const TP q = TP(__builtin_nan(""));
       x0 = q; x1 = q; x2 = q; y0 = q; y1 = q; y2 = q;
     }
-    store<true>(p, code, x0, x1, x2, y0, y1, y2);
+    store(p, code, x0, x1, x2, y0, y1, y2);
   }
-  // kNT: non-temporal state stores (else ordinary ones, for wavefronts that
-  // write pieces of lines which others complete)
-  template <bool kNT>
-  static __device__ __forceinline__ void st(TP* p, TP x) {
-    if (kNT) st_nt(p, x);
-    else *p = x;
-  }
-  template <bool kNT>
   __device__ __forceinline__ void store(int64_t p, uint32_t code, TP x0, TP x1, TP x2, TP y0, TP y1, TP y2) const {
     if (kOff32) {
       const uint32_t off = uint32_t(p) * uint32_t(sizeof(TP));
       char* rb = reinterpret_cast<char*>(r);
       char* vb = reinterpret_cast<char*>(v);
       const size_t stride = size_t(P) * sizeof(TP);
-      st<kNT>(reinterpret_cast<TP*>(rb + off), x0);
-      st<kNT>(reinterpret_cast<TP*>(rb + stride + off), x1);
-      st<kNT>(reinterpret_cast<TP*>(rb + 2 * stride + off), x2);
-      st<kNT>(reinterpret_cast<TP*>(vb + off), y0);
-      st<kNT>(reinterpret_cast<TP*>(vb + stride + off), y1);
-      st<kNT>(reinterpret_cast<TP*>(vb + 2 * stride + off), y2);
+      st_nt(reinterpret_cast<TP*>(rb + off), x0);
+      st_nt(reinterpret_cast<TP*>(rb + stride + off), x1);
+      st_nt(reinterpret_cast<TP*>(rb + 2 * stride + off), x2);
+      st_nt(reinterpret_cast<TP*>(vb + off), y0);
+      st_nt(reinterpret_cast<TP*>(vb + stride + off), y1);
+      st_nt(reinterpret_cast<TP*>(vb + 2 * stride + off), y2);
       // the code array seen in the global address space: the store then takes
       // its base from scalar registers and the 32-bit offset as it is
       typedef __attribute__((address_space(1))) uint8_t* GByte;
       *((GByte)err + uint32_t(p)) = uint8_t(code);
     } else {
-      st<kNT>(r + p, x0);
-      st<kNT>(r + P + p, x1);
-      st<kNT>(r + 2 * P + p, x2);
-      st<kNT>(v + p, y0);
-      st<kNT>(v + P + p, y1);
-      st<kNT>(v + 2 * P + p, y2);
+      st_nt(r + p, x0);
+      st_nt(r + P + p, x1);
+      st_nt(r + 2 * P + p, x2);
+      st_nt(v + p, y0);
+      st_nt(v + P + p, y1);
+      st_nt(v + 2 * P + p, y2);
       err[p] = uint8_t(code);
     }
   }

@@ -17,11 +17,11 @@
 namespace sgp4mi {
 
 // Register budget of the one-wavefront-per-tile kernels (the default dense and
-// ragged launches): the deep-space branch, taken by whole wavefronts of
-// deep-space satellites, holds more values than the near-Earth path and would
-// otherwise set every wavefront's allocation (74 registers, six wavefronts per
-// SIMD); asking for at least seven keeps eight, with the near-Earth path
-// compiled to the instructions it has without the branch.
+// ragged launches).  The deep-space branch, taken by whole wavefronts of
+// deep-space satellites, holds more values than the near-Earth path; seven
+// wavefronts per SIMD leave both without spills.  Eight gain 1.5 us of 72 at 9,341
+// x 1,000 mixed and lose 2 of 93 at 4,096 deep-space satellites x 1008 and 12 of
+// 1,258 at 100,000 x 1008 FP64; six change nothing or lose 2 us.
 #define SGP4MI_TILE_OCCUPANCY __attribute__((amdgpu_waves_per_eu(7, 8)))
 
 // ------------------------------------------------------------------ dense --
