@@ -108,7 +108,9 @@ __device__ __forceinline__ uint32_t point64_secular(const double* c, double t_ab
 __device__ __forceinline__ uint32_t point64_orbit(const double* c, const Grav& g, double t, double U, Point64& p) {
   const double a = p.a, ax = p.ax, ay = p.ay, ra = p.ra;
   double sp, cp;
-  const double iD0 = kepler64(U, ax, ay, &sp, &cp);
+  const double eb = fabs(ax) + fabs(ay);
+  const bool small = __all(eb <= kepler_small<double>());
+  const double iD0 = kepler64(U, ax, ay, eb, small, &sp, &cp);
   p.sp = sp;
   p.cp = cp;
   p.ecE = ax * cp + ay * sp;
@@ -147,7 +149,7 @@ __device__ __forceinline__ uint32_t point64_orbit(const double* c, const Grav& g
   p.csu = p.cosu;
   p.sinc = c[kSini];
   p.cinc = c[kCosi];
-  rotate_node64(&p.ssu, &p.csu, du, &p.sinc, &p.cinc, dinc, c[kI0]);
+  rotate_node64(&p.ssu, &p.csu, du, &p.sinc, &p.cinc, dinc, c[kI0], small);
   double node = fma(t, fma(t, c[kNodecf], c[kNodedot]), c[kNode0]);
   if (fabs(t) > kFarMin) node = wrap_pi(node);
   sincos_rr(node + kc * p.s2, &p.snod, &p.cnod);

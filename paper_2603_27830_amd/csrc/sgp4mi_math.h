@@ -194,7 +194,7 @@ __device__ __forceinline__ void sincos_rr(float x, float* s, float* c) {
 // revolutions): the angle is reduced to a fraction of a turn in its own type,
 // then rounded to float.
 __device__ __forceinline__ void sincos_hw(double x, float* s, float* c) {
-  const float r = float(__builtin_amdgcn_fract(x * kHalfAngle64[20]));
+  const float r = float(__builtin_amdgcn_fract(x * sgpr_const(0.15915494309189533577)));
   *s = __builtin_amdgcn_sinf(r);
   *c = __builtin_amdgcn_cosf(r);
 }
@@ -256,6 +256,14 @@ __device__ __forceinline__ void rotate_tiny(double* s, double* c, double d) {
   const double d2 = d * d;
   rotate_by(s, c, fma(d2 * sgpr_const(-1.66666666666666666667e-1), d, d),
             d2 * fma(d2, sgpr_const(4.16666666666666666667e-2), -0.5));
+}
+
+// Float: the sine through d, the cosine through d^2; the next terms are below
+// 4e-10 and 2e-13.
+__device__ __forceinline__ void rotate_tiny(float* s, float* c, float d) {
+  const float h = -0.5f * d * d, s0 = *s, c0 = *c;
+  *s = fmaf(c0, d, fmaf(s0, h, s0));
+  *c = fmaf(-s0, d, fmaf(c0, h, c0));
 }
 
 // Reciprocal and reciprocal square root: in double the hardware estimate y

@@ -170,6 +170,9 @@ __device__ __forceinline__ double vfma(double a, double b, double c) { return fm
 __device__ __forceinline__ float vfma(float a, float b, float c) { return fmaf(a, b, c); }
 __device__ __forceinline__ double vmax(double x, double y) { return fmax(x, y); }
 __device__ __forceinline__ float vmax(float x, float y) { return fmaxf(x, y); }
+// The eccentricity floor: x is below 1 and not NaN (one median-of-three in float).
+__device__ __forceinline__ double floor_ecc(double x) { return fmax(x, 1.0e-6); }
+__device__ __forceinline__ float floor_ecc(float x) { return __builtin_amdgcn_fmed3f(x, sgpr_const(1.0e-6f), 1.0f); }
 __device__ __forceinline__ double vabs(double x) { return fabs(x); }
 __device__ __forceinline__ float vabs(float x) { return fabsf(x); }
 __device__ __forceinline__ double arctan2(double y, double x) { return atan2(y, x); }
@@ -249,20 +252,23 @@ constexpr double kFarMin = 1.0e12;
 // FP64: sin and cos of the eccentric longitude psi, and an estimate (relative
 // error below 1e-5) of 1 / (1 - axn cos psi - ayn sin psi).
 //
-// Below kKeplerSmall (|axn| + |ayn|) the whole wavefront takes one step instead
-// of Newton's two: with s = f / f' at psi = U, S = axn sin U - ayn cos U, C = axn
+// Where eb = |axn| + |ayn| is at most kepler_small in every lane (small) the
+// wavefront takes one step instead of Newton's two: with s = f / f' at psi = U, S = axn sin U - ayn cos U, C = axn
 // cos U + ayn sin U and c = C / f', the offset solves
 //   d = s - (s / 2) d^2 - (c / 6) d^3 + (s / 24) d^4 + ...,
 // d = s - s^3 (1/2 + c/6) + (13/24) s^5 up to 0.43 c s^5 (3e-16 at the bound;
 // Newton ends with up to 5e-13).  At 100,000 x 1008 over a week the second
-// iteration cost 8 % of the kernel.
-constexpr double kKeplerSmall = 3.0e-3;
-__device__ __forceinline__ double kepler64(double U, double axn, double ayn, double* sp_, double* cp_) {
+// iteration cost 8 % of the kernel.  In float the bound is where Newton's first
+// step already ends the iteration (eb^3 below the tolerance).
+template <class T> __device__ __forceinline__ constexpr T kepler_small();
+template <> __device__ __forceinline__ constexpr double kepler_small<double>() { return 3.0e-3; }
+template <> __device__ __forceinline__ constexpr float kepler_small<float>() { return 4.5e-3f; }
+__device__ __forceinline__ double kepler64(double U, double axn, double ayn, double eb, bool small, double* sp_,
+                                           double* cp_) {
   double sp, cp;
   sincos_rr(U, &sp, &cp);
-  const double eb = fabs(axn) + fabs(ayn);
   double iD;
-  if (__all(eb <= kKeplerSmall)) {
+  if (small) {
     const double S = axn * sp - ayn * cp, C = axn * cp + ayn * sp;
     const double D = 1.0 - C;
     iD = __builtin_amdgcn_rcp(D);
@@ -294,11 +300,11 @@ __device__ __forceinline__ double kepler64(double U, double axn, double ayn, dou
 // O(delta^2), delta = |.|^2 - 1.  Orbits above the Earth's surface stay within
 // kRotTiny (|du| <= 8.2e-4 / p_L^2, |dinc| <= 4.1e-4 / p_L^2).
 __device__ __forceinline__ void rotate_node64(double* su, double* cu, double du, double* si, double* ci, double dinc,
-                                              double i0) {
+                                              double i0, bool small) {
   const double sinu = *su, cosu = *cu;
   const double n2 = sinu * sinu + cosu * cosu;
   double h = fma(n2, -0.5, 1.5);
-  if (fabs(n2 - 1.0) > 1.0e-8) h = rsq(n2);
+  if (!small && fabs(n2 - 1.0) > 1.0e-8) h = rsq(n2);  // (small eccentricities: rounding alone)
   double s = sinu * h, c = cosu * h;
   if (fmax(fabs(du), fabs(dinc)) <= kRotTiny) {
     rotate_tiny(&s, &c, du);
@@ -327,8 +333,10 @@ __device__ __forceinline__ void rotate_node64(double* su, double* cu, double du,
 // 1 / (1 - ecE), 1 / (1 + betal) and 1 / (1 - e^2).  FP64 is bound by vector
 // instructions (95 % of the cycles at 100,000 satellites x 1008 times): with
 // those, the folded short-period coefficients, the one-step Kepler solution, the
-// shorter rotations and the table index without a conversion a point takes 323 of
-// them, and that grid 1,364 us instead of 1,679.
+// shorter rotations, the table index without a conversion and the series in eL^2 a
+// point takes about 305 of them, and that grid 1,340 us instead of 1,679.  In float
+// the one-step solution, the series and the shorter rotations took 9,341 x 1,000
+// mixed from 72.5 to 69.5 us.
 template <class TS, class TP>
 __device__ __forceinline__ uint32_t sgp4_tail(const Grav& g, TP a, TP e, TS M, TS argp, TS node,
                                               const Incl<TS, TP>& q, PointState<TP>& out) {
@@ -338,11 +346,13 @@ __device__ __forceinline__ uint32_t sgp4_tail(const Grav& g, TP a, TP e, TS M, T
   TP sw, cw;
   TR::sc_damped(argp, &sw, &cw);
   const TP axn = e * cw;
-  TP ra, ia, tau;
+  const TP ra = rsq(a), ia = ra * ra;
+  TP tau;
   if constexpr (kDouble) {
-    ra = rsq(a);
-    ia = ra * ra;
-    tau = ia * rcp(fma(-e, e, 1.0));
+    const TP e2 = e * e;
+    // 1 / (1 - e^2) through e^4 (the next term is below 8e-16 there)
+    if (__all(e <= kepler_small<TP>())) tau = fma(ia, fma(e2, e2, e2), ia);
+    else tau = ia * rcp(1.0 - e2);
   } else {
     tau = rcp(a * (TP(1) - e * e));
   }
@@ -358,22 +368,27 @@ __device__ __forceinline__ uint32_t sgp4_tail(const Grav& g, TP a, TP e, TS M, T
   // U = L_T - node, with the mean longitude L = M + argp + node and its J3
   // long-period correction L_T = L + tau L_cof a_xN: node cancels.
   const TS U = M + argp + TS(tau * q.Lcof * axn);
+  const TP eb = vabs(axn) + vabs(ayn);
+  const bool small = __all(eb <= kepler_small<TP>());
   TP sp, cp, iD0;
   if constexpr (kDouble) {
-    iD0 = kepler64(U, axn, ayn, &sp, &cp);
+    iD0 = kepler64(U, axn, ayn, eb, small, &sp, &cp);
   } else {
     TR::sc(U, &sp, &cp);
-    TP dpsi = TP(0);
-    const TP eb = vabs(axn) + vabs(ayn);
-    const KeplerExit<TP> done(eb);
-    const TP hi = step_bound();
-    for (int k = 0; k < 10; ++k) {
-      TP step = (axn * sp - ayn * cp - dpsi) * rcp(TP(1) - axn * cp - ayn * sp);
-      step = clamp_step(step, hi);
-      dpsi = k == 0 ? step : dpsi + step;  // no 0 + step
-      if (vabs(step) <= TP(kRotMax)) rotate_small(&sp, &cp, step);
-      else TR::sc(U + TS(dpsi), &sp, &cp);
-      if (__all(done(vabs(step)))) break;
+    if (small) {
+      rotate_small(&sp, &cp, (axn * sp - ayn * cp) * rcp(TP(1) - axn * cp - ayn * sp));
+    } else {
+      TP dpsi = TP(0);
+      const KeplerExit<TP> done(eb);
+      const TP hi = step_bound();
+      for (int k = 0; k < 10; ++k) {
+        TP step = (axn * sp - ayn * cp - dpsi) * rcp(TP(1) - axn * cp - ayn * sp);
+        step = clamp_step(step, hi);
+        dpsi = k == 0 ? step : dpsi + step;  // no 0 + step
+        if (vabs(step) <= TP(kRotMax)) rotate_small(&sp, &cp, step);
+        else TR::sc(U + TS(dpsi), &sp, &cp);
+        if (__all(done(vabs(step)))) break;
+      }
     }
   }
 
@@ -381,33 +396,40 @@ __device__ __forceinline__ uint32_t sgp4_tail(const Grav& g, TP a, TP e, TS M, T
   const TP ecE = axn * cp + ayn * sp;
   const TP esE = axn * sp - ayn * cp;
   const TP eL2 = axn * axn + ayn * ayn;
-  TP rl, ar, rdotl, rvdotl, betal, inv_pl;
-  if constexpr (kDouble) {
-    const TP om = 1.0 - eL2;
-    if (!(om >= 0.0)) return 4;  // a > 0 here
-    const TP D = 1.0 - ecE;
-    rl = a * D;
-    ar = rcp_from(D, iD0);
-    const TP sr = ra * ar;  // sqrt(a) / r_l
-    const TP rb = rsq(om);
-    betal = om * rb;
-    rdotl = sr * esE;
-    rvdotl = sr * betal;
-    inv_pl = ia * (rb * rb);
+  const TP D = TP(1) - ecE;
+  const TP rl = a * D;
+  TP ar, betal, iopb, inv_pl;  // 1 / D, beta = sqrt(1 - eL^2), 1 / (1 + beta), 1 / (a beta^2)
+  if constexpr (kDouble) ar = rcp_from(D, iD0);
+  else ar = rcp(D);
+  if (small) {
+    // eL^2 <= 9e-6 (2.1e-5 in float): the series in eL^2, the next terms below
+    // 5e-17 (3e-10; 1 / beta^2 8e-21 and 5e-10)
+    if constexpr (kDouble) {
+      betal = fma(eL2, fma(eL2, sgpr_const(-0.125), -0.5), 1.0);
+      iopb = fma(eL2, fma(eL2, 0.0625, 0.125), 0.5);
+      inv_pl = ia * fma(eL2, fma(eL2, 1.0 + eL2, 1.0), 1.0);
+    } else {
+      betal = fmaf(eL2, -0.5f, 1.0f);
+      iopb = fmaf(eL2, sgpr_const(0.125f), 0.5f);
+      inv_pl = fmaf(ia, eL2, ia);
+    }
   } else {
-    const TP pL = a * (TP(1) - eL2);
-    if (!(pL >= TP(0))) return 4;
-    rl = a * (TP(1) - ecE);
-    const TP inv_rl = rcp(rl);
-    ra = rsq(a);
-    const TP sqa = a * ra;
-    rdotl = sqa * esE * inv_rl;
-    betal = sq_root(TP(1) - eL2);
-    rvdotl = sqa * betal * inv_rl;  // sqrt(pL) = sqrt(a) * sqrt(1 - eL^2)
-    ar = a * inv_rl;
-    inv_pl = rcp(pL);
+    const TP om = TP(1) - eL2;
+    if (!(om >= TP(0))) return 4;  // a > 0 here
+    if constexpr (kDouble) {
+      const TP rb = rsq(om);
+      betal = om * rb;
+      inv_pl = ia * (rb * rb);
+    } else {
+      betal = sq_root(om);
+      inv_pl = rcp(a * om);
+    }
+    iopb = rcp(TP(1) + betal);
   }
-  const TP w = esE * rcp(TP(1) + betal);
+  const TP sr = ra * ar;  // sqrt(a) / r_l
+  const TP rdotl = sr * esE;
+  const TP rvdotl = sr * betal;  // sqrt(p_L) / r_l
+  const TP w = esE * iopb;
   const TP sinu = ar * (sp - ayn - axn * w);
   const TP cosu = ar * (cp - axn + ayn * w);
   const TP sin2u = TP(2) * sinu * cosu;
@@ -415,7 +437,7 @@ __device__ __forceinline__ uint32_t sgp4_tail(const Grav& g, TP a, TP e, TS M, T
 
   // Short-period periodics (J2): k2 / p_L and k2 / p_L^2 times the inclination
   // functions, k2 in the coefficients.
-  const TP nk = ra * ra * ra;  // n / ke = a^-3/2
+  const TP nk = ra * ia;  // n / ke = a^-3/2
   const TP ip2 = inv_pl * inv_pl;
   const TP ni = nk * inv_pl;
   const TP s2 = ip2 * sin2u, c2 = ip2 * cos2u;
@@ -429,21 +451,23 @@ __device__ __forceinline__ uint32_t sgp4_tail(const Grav& g, TP a, TP e, TS M, T
   // Orientation: sin/cos of u_k = u + du, i_k = i0 + dinc, node_k = node + dnode.
   TP ssu = sinu, csu = cosu, sinc = q.sini, cinc = q.cosi;
   if constexpr (kDouble) {
-    rotate_node64(&ssu, &csu, du, &sinc, &cinc, dinc, q.i0);
+    rotate_node64(&ssu, &csu, du, &sinc, &cinc, dinc, q.i0, small);
   } else {
-    if (vabs(du) <= TP(kRotMax)) {
-      // (sinu, cosu) is a unit vector up to rounding (~1e-6 at most): one
-      // Newton step from 1 normalises it
-      const TP n2 = sinu * sinu + cosu * cosu;
-      const TP h = TP(1.5) - TP(0.5) * n2;
-      ssu = sinu * h;
-      csu = cosu * h;
-      rotate_small(&ssu, &csu, du);
+    // (sinu, cosu) is a unit vector up to rounding (~1e-6 at most): one Newton
+    // step from 1 normalises it
+    const TP n2 = sinu * sinu + cosu * cosu;
+    const TP h = TP(1.5) - TP(0.5) * n2;
+    ssu = sinu * h;
+    csu = cosu * h;
+    if (fmaxf(vabs(du), vabs(dinc)) <= TP(kRotTiny)) {
+      rotate_tiny(&ssu, &csu, du);
+      rotate_tiny(&sinc, &cinc, dinc);
     } else {
-      TR::sc(TS(arctan2(sinu, cosu) + du), &ssu, &csu);
+      if (vabs(du) <= TP(kRotMax)) rotate_small(&ssu, &csu, du);
+      else TR::sc(TS(arctan2(sinu, cosu) + du), &ssu, &csu);
+      if (vabs(dinc) <= TP(kRotMax)) rotate_small(&sinc, &cinc, dinc);
+      else TR::sc(TS(q.i0 + dinc), &sinc, &cinc);
     }
-    if (vabs(dinc) <= TP(kRotMax)) rotate_small(&sinc, &cinc, dinc);
-    else TR::sc(TS(q.i0 + dinc), &sinc, &cinc);
   }
   TP snod, cnod;
   TR::sc(node + TS(dnode), &snod, &cnod);
@@ -787,9 +811,8 @@ __device__ __forceinline__ uint32_t sgp4_point(const SatC<TS, TP>& c, const Grav
   // Angles stay unreduced: every one of them only enters through sin/cos,
   // whose own reduction handles any size met here.
 
-  // Eccentricity floor 1e-6.  e_s is not NaN here, so the maximum is the
-  // floor: one instruction in float instead of a compare and two selects.
-  const TP e = vmax(e_s, TP(1.0e-6));
+  // Eccentricity floor 1e-6.
+  const TP e = floor_ecc(e_s);
   const Incl<TS, TP> q{c.cosi, c.sini, c.i0, c.aycof, c.Lcof,
                        c.spA1, c.spX1h, c.spX1k, c.spX7q, c.spCN, c.spCI};
   return sgp4_tail<TS, TP>(g, a, e, M, argp, node, q, out);
@@ -800,6 +823,20 @@ template <bool kVec>
 __device__ __forceinline__ uint32_t load_info(const RecordView& rv, int64_t i) {
   if (kVec) return lane_slot(rv.slots + i)->info;
   return ((CSlot)(rv.slots + i))->info;
+}
+
+// Makes the info word, which the branches on it read, depend on the satellite's
+// other constants and on the time: the wavefront waits once for all of them.  Left
+// to itself the compiler moves those loads behind the branches, where they wait
+// for memory a second time.  For the float types of the kernels without the
+// deep-space terms: 700,000 tiles of ragged lists 420 -> 370 us (with the tile's
+// words read at once).  FP64 constants fill the scalar file, and beside the
+// deep-space terms the slot's address no longer fits it (4,096 deep-space
+// satellites 93 -> 97 us, for 2 of 70 at 9,341 x 1,000).
+template <class TS, class TP>
+__device__ __forceinline__ void loaded_together(SatC<TS, TP>& c, double t_abs) {
+  asm("" : "+s"(c.info) : "v"(t_abs), "s"(c.M0), "s"(c.t2cof), "s"(c.n0pp), "s"(c.epoch_min), "s"(c.eta), "s"(c.spA1),
+      "s"(c.pD3), "s"(c.pA0pp));
 }
 
 // Point of satellite i at t_abs: near-Earth, or the deep-space path.
@@ -816,7 +853,8 @@ template <class TS, class TP, bool kVec, bool kDeep = true>
 __device__ __forceinline__ uint32_t propagate_point(const RecordView& rv, int64_t i, const Grav& g, double t_abs,
                                                     PointState<TP>& out) {
   if (!kDeep || !record_has_deep(rv)) {
-    const SatC<TS, TP> c = load_sat<TS, TP, kVec>(rv, i);
+    SatC<TS, TP> c = load_sat<TS, TP, kVec>(rv, i);
+    if constexpr (!kVec && sizeof(TP) == 4 && !kDeep) loaded_together(c, t_abs);
     if (c.info & kInfoDeep) {
       out.ok = false;
       return 7u;

@@ -135,9 +135,11 @@ __global__ void __launch_bounds__(kBlock) SGP4MI_TILE_OCCUPANCY tile_once_kernel
   const int lane = threadIdx.x & 63;
   const int64_t w = int64_t(blockIdx.x) * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (w >= ntiles) return;
-  const int64_t start = tile_start[w];
-  const int32_t sat = tile_meta[2 * w];
-  const int32_t len = tile_meta[2 * w + 1];
+  int64_t start = tile_start[w];
+  int32_t sat = tile_meta[2 * w];
+  int32_t len = tile_meta[2 * w + 1];
+  // one wait for the three words (the branch on the length alone would come first)
+  asm("" : "+s"(len), "+s"(start), "+s"(sat));
   if (lane >= len) return;
   const Grav g = load_grav(rv);
   const int64_t p = kOff32 ? int64_t(uint32_t(start) + uint32_t(lane)) : start + lane;  // kOff32: p < 2^30
