@@ -19,13 +19,14 @@
 namespace sgp4mi {
 
 constexpr int kFusedTT = 16;
-// Satellites and lanes of a workgroup: half of its wavefronts initialise while
-// the others wait, and several workgroups on a compute unit fill the gaps.
-// Measured at 300,007 x 19 mixed (1M x 8 FP64): 64 and 128 lanes 65 (206) us, 128
-// and 256 66 (208), 256 and 256 72 (192, but 23 against 16 at 30,000 x 8), 128 and
-// 512 72 (242).
+// Satellites of a workgroup: one wavefront initialises while the others wait, and
+// several workgroups on a compute unit fill the gaps.  128 lanes up to kFusedNarrow
+// times of a workgroup, 256 beyond: 1M x 8 FP64 164 us with 128 and 182 with 256,
+// 300,000 x 2 mixed 17 and 20, but 300,007 x 19 mixed 57 and 51, 20,000 x 200 FP64
+// 103 and 88.  (128 satellites on 256 lanes 66 us where 64 on 128 took 65, 256 on
+// 256 72.)
 constexpr int kFusedSats = 64;
-constexpr int kFusedBlock = 128;
+constexpr int kFusedNarrow = 8;
 
 struct FusedArgs {
   int64_t n, T;
@@ -211,11 +212,11 @@ SGP4MI_LDS_REC(float, float)
 
 // kFusedSats satellites, times [y per, (y + 1) per) of the list.  Bound by VALU
 // issue.  One wavefront of sixteen initialising for 64 satellites, in runs of 16
-// times, took 204 us at 300,007 x 19 mixed, this 62; a lane per satellite walking
+// times, took 204 us at 300,007 x 19 mixed, this 51; a lane per satellite walking
 // its times in registers, outputs regrouped through LDS by eight times, 107
-// (pieces of cache lines); 1M x 8 FP64 242 -> 185, 300,000 x 2 mixed 33 -> 17.
-template <class TS, class TP, bool kOff32>
-__global__ void __launch_bounds__(kFusedBlock) __attribute__((amdgpu_waves_per_eu(4)))
+// (pieces of cache lines); 1M x 8 FP64 240 -> 164, 300,000 x 2 mixed 32 -> 17.
+template <class TS, class TP, bool kOff32, int kBlock>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4)))
     fused_kernel(FusedArgs a, Out<TP, kOff32> out) {
   __shared__ __align__(16) LdsSat<TS, TP> sats[kFusedSats];
   const int64_t i0 = int64_t(blockIdx.x) * kFusedSats;
@@ -233,7 +234,7 @@ __global__ void __launch_bounds__(kFusedBlock) __attribute__((amdgpu_waves_per_e
   __syncthreads();
   const int64_t t0 = int64_t(blockIdx.y) * a.per;
   const int32_t nt = int32_t(t0 + a.per < a.T ? a.per : a.T - t0);
-  const int32_t step_s = kFusedBlock / nt, step_j = kFusedBlock - step_s * nt;  // one pass further: satellites, times
+  const int32_t step_s = kBlock / nt, step_j = kBlock - step_s * nt;  // one pass further: satellites, times
   int32_t s = int32_t(threadIdx.x) / nt, j = int32_t(threadIdx.x) - s * nt;
   while (s < ns) {
     const LdsSat<TS, TP>* const p = &sats[s];
@@ -269,7 +270,10 @@ static void fused_go(const FusedArgs& a, void* r, void* v, uint8_t* err, hipStre
     return;
   }
   const dim3 grid(unsigned((a.n + kFusedSats - 1) / kFusedSats), unsigned((a.T + a.per - 1) / a.per));
-  hipLaunchKernelGGL((fused_kernel<TS, TP, kOff32>), grid, dim3(kFusedBlock), 0, s, a, o);
+  if (a.per <= kFusedNarrow)
+    hipLaunchKernelGGL((fused_kernel<TS, TP, kOff32, 128>), grid, dim3(128), 0, s, a, o);
+  else
+    hipLaunchKernelGGL((fused_kernel<TS, TP, kOff32, 256>), grid, dim3(256), 0, s, a, o);
 }
 
 template <class TS, class TP>
@@ -299,8 +303,10 @@ hipError_t launch_fused(int precision, const double g[5], double ref_day, int64_
   a.grav = grav_in(g);
   a.vkms = a.grav.radius * a.grav.ke / 60.0;
   a.ref_day = ref_day;
-  // enough workgroups to fill the chip, as far as there are times
-  const int64_t wgs = (n + kFusedSats - 1) / kFusedSats, groups = std::min<int64_t>(T, (1024 + wgs - 1) / wgs);
+  // Two workgroups per CU, as far as there are times: every further split of the
+  // times initialises the satellites once more (60,000 x 4 FP64: 17.4 us at four
+  // per CU, 15.7 at two; 20,000 x 64 30 us at two, 38 at one).
+  const int64_t wgs = (n + kFusedSats - 1) / kFusedSats, groups = std::min<int64_t>(T, (512 + wgs - 1) / wgs);
   a.per = (T + groups - 1) / groups;
   switch (precision) {
     case 0: fused_t<double, double>(a, r, v, err, s); break;
