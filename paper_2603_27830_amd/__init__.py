@@ -38,12 +38,23 @@ def _out_dtype(p: int) -> torch.dtype:
     return torch.float64 if p == _native.SGP4_FP64 else torch.float32
 
 
-def _stream(device) -> int:
-    return torch.cuda.current_stream(device).cuda_stream
-
-
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+def _launch(device, what, f, *args):
+    """f(*args, the device's current stream) with the device current.  A small
+    call is bound by this path: the stream's handle is read without a Stream
+    object and the device is only switched when it is another one (64 x 100:
+    27 -> 19 us for initialisation and propagation)."""
+    i = device.index
+    if torch.cuda.current_device() == i:
+        rc = f(*args, torch._C._cuda_getCurrentRawStream(i))
+    else:
+        with torch.cuda.device(device):
+            rc = f(*args, torch._C._cuda_getCurrentRawStream(i))
+    if rc != 0:
+        _native.check(rc, what)
 
 
 def _need(t: torch.Tensor, dtype, name, device=None):
@@ -89,10 +100,9 @@ def init(elem: torch.Tensor, grav: Optional[Sequence[float]] = None, ref_jd=None
     g = None
     if grav is not None:
         g = (ctypes.c_double * 5)(*[float(x) for x in grav])
-    with torch.cuda.device(elem.device):
-        _native.check(_native.lib().sgp4_init_ex(g, _ref(ref_jd), n, _ptr(elem), _ptr(consts), _ptr(flags),
-                                                 _stream(elem.device)), "sgp4_init_ex")
-    return Record(consts, n, flags[:n], elem)
+    _launch(elem.device, "sgp4_init_ex", _native.lib().sgp4_init_ex, g, _ref(ref_jd), n, _ptr(elem), _ptr(consts),
+            _ptr(flags))
+    return Record(consts, n, flags if n else flags[:0], elem)
 
 
 def propagate(rec: Record, t: torch.Tensor, precision="fp64", out=None, block: Optional[int] = None):
@@ -100,23 +110,21 @@ def propagate(rec: Record, t: torch.Tensor, precision="fp64", out=None, block: O
     block: None for the library's default launch (sgp4_propagate), else the launch
     configuration word of sgp4_propagate_ex (workgroup size and flags)."""
     p = _prec(precision)
-    _need(t, torch.float64, "t", rec.device)
+    device = rec.device
+    _need(t, torch.float64, "t", device)
     n, T = rec.n, int(t.numel())
     if out is None:
         dt = _out_dtype(p)
-        r = torch.empty((3, n, T), dtype=dt, device=rec.device)
-        v = torch.empty((3, n, T), dtype=dt, device=rec.device)
-        err = torch.empty((n, T), dtype=torch.uint8, device=rec.device)
+        r = torch.empty((3, n, T), dtype=dt, device=device)
+        v = torch.empty((3, n, T), dtype=dt, device=device)
+        err = torch.empty((n, T), dtype=torch.uint8, device=device)
     else:
         r, v, err = out
-    with torch.cuda.device(rec.device):
-        if block is None:
-            rc = _native.lib().sgp4_propagate(_ptr(rec.consts), n, _ptr(t), T, p, _ptr(r), _ptr(v), _ptr(err),
-                                              _stream(rec.device))
-        else:
-            rc = _native.lib().sgp4_propagate_ex(_ptr(rec.consts), n, _ptr(t), T, p, _ptr(r), _ptr(v), _ptr(err),
-                                                 int(block), _stream(rec.device))
-        _native.check(rc, "sgp4_propagate")
+    args = (_ptr(rec.consts), n, _ptr(t), T, p, _ptr(r), _ptr(v), _ptr(err))
+    if block is None:
+        _launch(device, "sgp4_propagate", _native.lib().sgp4_propagate, *args)
+    else:
+        _launch(device, "sgp4_propagate", _native.lib().sgp4_propagate_ex, *args, int(block))
     return r, v, err
 
 
@@ -142,22 +150,18 @@ class RaggedPlan:
         r, v, err = self.out
         h = ctypes.c_void_p()
         flags = (PLAN_AUTOTUNE if autotune else 0) | (PLAN_GRAPH if graph else 0)
-        with torch.cuda.device(rec.device):
-            if config is None:
-                rc = _native.lib().sgp4_plan_create(ctypes.byref(h), _ptr(rec.consts), rec.n, _ptr(offsets), _ptr(t),
-                                                    self.nnz, self.p, _ptr(r), _ptr(v), _ptr(err), flags,
-                                                    _stream(rec.device))
-            else:
-                mode, block, per_cu = (int(x) for x in config)
-                rc = _native.lib().sgp4_plan_create_config(ctypes.byref(h), _ptr(rec.consts), rec.n, _ptr(offsets),
-                                                           _ptr(t), self.nnz, self.p, _ptr(r), _ptr(v), _ptr(err),
-                                                           mode, block, per_cu, flags, _stream(rec.device))
-            _native.check(rc, "sgp4_plan_create")
+        args = (ctypes.byref(h), _ptr(rec.consts), rec.n, _ptr(offsets), _ptr(t), self.nnz, self.p, _ptr(r), _ptr(v),
+                _ptr(err))
+        if config is None:
+            _launch(rec.device, "sgp4_plan_create", _native.lib().sgp4_plan_create, *args, flags)
+        else:
+            mode, block, per_cu = (int(x) for x in config)
+            _launch(rec.device, "sgp4_plan_create", _native.lib().sgp4_plan_create_config, *args, mode, block, per_cu,
+                    flags)
         self.handle = h
 
     def launch(self):
-        with torch.cuda.device(self.rec.device):
-            _native.check(_native.lib().sgp4_plan_launch(self.handle, _stream(self.rec.device)), "sgp4_plan_launch")
+        _launch(self.rec.device, "sgp4_plan_launch", _native.lib().sgp4_plan_launch, self.handle)
         return self.out
 
     def describe(self) -> str:
@@ -210,10 +214,8 @@ def propagate_elements(elem: torch.Tensor, t: torch.Tensor, precision="fp64", gr
         _need(flags, torch.uint8, "flags", elem.device)
         if flags.numel() < n:
             raise ValueError("flags must hold n entries")
-    with torch.cuda.device(elem.device):
-        _native.check(_native.lib().sgp4_propagate_elements_ex(
-            g, _ref(ref_jd), n, _ptr(elem), _ptr(t), T, p, _ptr(r), _ptr(v), _ptr(err), _ptr(flags), _ptr(workspace),
-            ws_bytes, _stream(elem.device)), "sgp4_propagate_elements_ex")
+    _launch(elem.device, "sgp4_propagate_elements_ex", _native.lib().sgp4_propagate_elements_ex, g, _ref(ref_jd), n,
+            _ptr(elem), _ptr(t), T, p, _ptr(r), _ptr(v), _ptr(err), _ptr(flags), _ptr(workspace), ws_bytes)
     return r, v, err
 
 
@@ -240,10 +242,8 @@ def screen(r: torch.Tensor, dist_km: float, err: Optional[torch.Tensor] = None, 
     wsb = int(L.sgp4_screen_workspace_bytes(n, T))
     ws = torch.empty(max(wsb, 1), dtype=torch.uint8, device=r.device)
     prec = _native.SGP4_FP64 if r.dtype == torch.float64 else _native.SGP4_FP32
-    with torch.cuda.device(r.device):
-        _native.check(L.sgp4_screen_ex(_ptr(r), prec, _ptr(err), n, T, float(dist_km), cap, _ptr(pairs),
-                                       _ptr(dist), _ptr(count), _ptr(ws), wsb, int(mode), _stream(r.device)),
-                      "sgp4_screen")
+    _launch(r.device, "sgp4_screen", L.sgp4_screen_ex, _ptr(r), prec, _ptr(err), n, T, float(dist_km), cap, _ptr(pairs),
+            _ptr(dist), _ptr(count), _ptr(ws), wsb, int(mode))
     total = int(count.item())
     m = min(total, cap)
     return pairs[:m], dist[:m], total
@@ -275,10 +275,8 @@ def screen_noalloc(r: torch.Tensor, dist_km: float, err: Optional[torch.Tensor] 
     _need(count, torch.int64, "count", r.device)
     cap = int(min(pairs.shape[0], dist.shape[0]))
     prec = _native.SGP4_FP64 if r.dtype == torch.float64 else _native.SGP4_FP32
-    with torch.cuda.device(r.device):
-        _native.check(_native.lib().sgp4_screen_noalloc(_ptr(r), prec, _ptr(err), n, T, float(dist_km), cap,
-                                                        _ptr(pairs), _ptr(dist), _ptr(count), _stream(r.device)),
-                      "sgp4_screen_noalloc")
+    _launch(r.device, "sgp4_screen_noalloc", _native.lib().sgp4_screen_noalloc, _ptr(r), prec, _ptr(err), n, T,
+            float(dist_km), cap, _ptr(pairs), _ptr(dist), _ptr(count))
     total = int(count.item())
     m = min(total, cap)
     return pairs[:m], dist[:m], total
@@ -328,15 +326,18 @@ def propagate_ragged(rec: Record, offsets: torch.Tensor, t: torch.Tensor, precis
     else:
         r, v, err = out if out is not None else _ragged_out(p, nnz, rec.device)
         handle = None
-    with torch.cuda.device(rec.device):
-        _native.check(_native.lib().sgp4_propagate_ragged(_ptr(rec.consts), rec.n, _ptr(offsets), _ptr(t), nnz, p,
-                                                          _ptr(r), _ptr(v), _ptr(err), handle, _stream(rec.device)),
-                      "sgp4_propagate_ragged")
+    _launch(rec.device, "sgp4_propagate_ragged", _native.lib().sgp4_propagate_ragged, _ptr(rec.consts), rec.n,
+            _ptr(offsets), _ptr(t), nnz, p, _ptr(r), _ptr(v), _ptr(err), handle)
     return r, v, err
 
 
 def vjp(rec: Record, t: torch.Tensor, gr: torch.Tensor, gv: Optional[torch.Tensor] = None, precision="fp64"):
     """Vector-Jacobian product of the dense propagation: float64 [7, n]."""
+    return _vjp(rec, t, gr, gv, precision, 7)
+
+
+def _vjp(rec, t, gr, gv, precision, rows):
+    """vjp into the first seven rows of a new [rows, n]."""
     p = _prec(precision)
     _need(t, torch.float64, "t", rec.device)
     dt = _out_dtype(p)
@@ -350,10 +351,9 @@ def vjp(rec: Record, t: torch.Tensor, gr: torch.Tensor, gv: Optional[torch.Tenso
         _need(gv, dt, "gv", rec.device)
         if gv.numel() != 3 * n * T:
             raise ValueError("gv must have 3*n*T elements")
-    out = torch.empty((7, n), dtype=torch.float64, device=rec.device)
-    with torch.cuda.device(rec.device):
-        _native.check(_native.lib().sgp4_vjp(n, _ptr(rec.elem), _ptr(rec.consts), _ptr(t), T, p, _ptr(gr), _ptr(gv),
-                                             _ptr(out), _stream(rec.device)), "sgp4_vjp")
+    out = torch.empty((rows, n), dtype=torch.float64, device=rec.device)
+    _launch(rec.device, "sgp4_vjp", _native.lib().sgp4_vjp, n, _ptr(rec.elem), _ptr(rec.consts), _ptr(t), T, p, _ptr(gr),
+            _ptr(gv), _ptr(out))
     return out
 
 
@@ -361,6 +361,10 @@ def vjp_ragged(rec: Record, offsets: torch.Tensor, t: torch.Tensor, gr: torch.Te
                gv: Optional[torch.Tensor] = None, precision="fp64"):
     """Vector-Jacobian product over per-satellite time lists (CSR offsets
     int64 [n + 1], times float64 [nnz], cotangents [3, nnz]): float64 [7, n]."""
+    return _vjp_ragged(rec, offsets, t, gr, gv, precision, 7)
+
+
+def _vjp_ragged(rec, offsets, t, gr, gv, precision, rows):
     p = _prec(precision)
     _need(offsets, torch.int64, "offsets", rec.device)
     _need(t, torch.float64, "t", rec.device)
@@ -377,11 +381,9 @@ def vjp_ragged(rec: Record, offsets: torch.Tensor, t: torch.Tensor, gr: torch.Te
         _need(gv, dt, "gv", rec.device)
         if gv.numel() != 3 * nnz:
             raise ValueError("gv must have 3*nnz elements")
-    out = torch.empty((7, n), dtype=torch.float64, device=rec.device)
-    with torch.cuda.device(rec.device):
-        _native.check(_native.lib().sgp4_vjp_ragged(n, _ptr(rec.elem), _ptr(rec.consts), _ptr(offsets), _ptr(t), nnz,
-                                                    p, _ptr(gr), _ptr(gv), _ptr(out), _stream(rec.device)),
-                      "sgp4_vjp_ragged")
+    out = torch.empty((rows, n), dtype=torch.float64, device=rec.device)
+    _launch(rec.device, "sgp4_vjp_ragged", _native.lib().sgp4_vjp_ragged, n, _ptr(rec.elem), _ptr(rec.consts),
+            _ptr(offsets), _ptr(t), nnz, p, _ptr(gr), _ptr(gv), _ptr(out))
     return out
 
 
@@ -395,9 +397,8 @@ def jacobian(rec: Record, t: torch.Tensor, precision="fp64", out: Optional[torch
         out = torch.empty((6, 7, n, T), dtype=torch.float64, device=rec.device)
     elif out.dtype != torch.float64 or out.numel() != 42 * n * T or not out.is_contiguous():
         raise ValueError("out must be a contiguous float64 tensor of 42*n*T elements")
-    with torch.cuda.device(rec.device):
-        _native.check(_native.lib().sgp4_jacobian(n, _ptr(rec.elem), _ptr(rec.consts), _ptr(t), T, p, _ptr(out),
-                                                  _stream(rec.device)), "sgp4_jacobian")
+    _launch(rec.device, "sgp4_jacobian", _native.lib().sgp4_jacobian, n, _ptr(rec.elem), _ptr(rec.consts), _ptr(t), T, p,
+            _ptr(out))
     return out
 
 
@@ -415,10 +416,8 @@ def jacobian_ragged(rec: Record, offsets: torch.Tensor, t: torch.Tensor, precisi
         out = torch.empty((6, 7, nnz), dtype=torch.float64, device=rec.device)
     elif out.dtype != torch.float64 or out.numel() != 42 * nnz or not out.is_contiguous():
         raise ValueError("out must be a contiguous float64 tensor of 42*nnz elements")
-    with torch.cuda.device(rec.device):
-        _native.check(_native.lib().sgp4_jacobian_ragged(rec.n, _ptr(rec.elem), _ptr(rec.consts), _ptr(offsets),
-                                                         _ptr(t), nnz, p, _ptr(out), _stream(rec.device)),
-                      "sgp4_jacobian_ragged")
+    _launch(rec.device, "sgp4_jacobian_ragged", _native.lib().sgp4_jacobian_ragged, rec.n, _ptr(rec.elem),
+            _ptr(rec.consts), _ptr(offsets), _ptr(t), nnz, p, _ptr(out))
     return out
 
 
@@ -432,6 +431,7 @@ class SGP4Function(torch.autograd.Function):
         r, v, err = propagate(rec, t, precision)
         ctx.rec, ctx.t, ctx.precision = rec, t, precision
         ctx.mark_non_differentiable(err)
+        ctx.set_materialize_grads(False)  # an unused output's cotangent stays None: no zeros written, none read
         return r, v, err
 
     @staticmethod
@@ -440,9 +440,8 @@ class SGP4Function(torch.autograd.Function):
         dt = _out_dtype(_prec(p))
         if gr is None:
             gr = torch.zeros((3, ctx.rec.n, ctx.t.numel()), dtype=dt, device=ctx.rec.device)
-        g7 = vjp(ctx.rec, ctx.t, gr.to(dt), None if gv is None else gv.to(dt), p)
-        g = torch.zeros((8, ctx.rec.n), dtype=torch.float64, device=ctx.rec.device)
-        g[:7] = g7
+        g = _vjp(ctx.rec, ctx.t, gr.to(dt), None if gv is None else gv.to(dt), p, 8)
+        g[7].zero_()
         return g, None, None, None
 
 
@@ -457,6 +456,7 @@ class SGP4RaggedFunction(torch.autograd.Function):
         r, v, err = propagate_ragged(rec, offsets, t, precision)
         ctx.rec, ctx.offsets, ctx.t, ctx.precision = rec, offsets, t, precision
         ctx.mark_non_differentiable(err)
+        ctx.set_materialize_grads(False)  # an unused output's cotangent stays None: no zeros written, none read
         return r, v, err
 
     @staticmethod
@@ -465,7 +465,6 @@ class SGP4RaggedFunction(torch.autograd.Function):
         dt = _out_dtype(_prec(p))
         if gr is None:
             gr = torch.zeros((3, ctx.t.numel()), dtype=dt, device=ctx.rec.device)
-        g7 = vjp_ragged(ctx.rec, ctx.offsets, ctx.t, gr.to(dt), None if gv is None else gv.to(dt), p)
-        g = torch.zeros((8, ctx.rec.n), dtype=torch.float64, device=ctx.rec.device)
-        g[:7] = g7
+        g = _vjp_ragged(ctx.rec, ctx.offsets, ctx.t, gr.to(dt), None if gv is None else gv.to(dt), p, 8)
+        g[7].zero_()
         return g, None, None, None, None
