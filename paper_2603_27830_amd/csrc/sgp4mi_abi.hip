@@ -183,7 +183,7 @@ std::string tune_key(const sgp4_plan* p) {
   if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess) arch = prop.gcnArchName;
   for (auto& ch : arch) if (ch == ' ' || ch == ':') ch = '_';
   char buf[256];
-  std::snprintf(buf, sizeof buf, "v4/%s/p%d/d%d/n%d/z%d", arch.c_str(), p->precision, p->deep ? 1 : 0,
+  std::snprintf(buf, sizeof buf, "v5/%s/p%d/d%d/n%d/z%d", arch.c_str(), p->precision, p->deep ? 1 : 0,
                 int(std::log2(double(p->n) + 1)), int(std::log2(double(p->nnz) + 1)));
   return buf;
 }

@@ -56,7 +56,8 @@ template <class Off>
 SGP4MI_HD inline int64_t point_owner(const Off& offsets, int64_t n, int64_t first, int64_t p, bool* owned) {
   int64_t sat = first < 0 ? 0 : (first >= n ? n - 1 : first);
   while (sat + 1 < n && offsets[sat + 1] <= p) ++sat;
-  *owned = offsets[sat] <= p && p < offsets[sat + 1];
+  const int64_t begin = offsets[sat], end = offsets[sat + 1];  // both loads before the first comparison
+  *owned = (begin <= p) & (p < end);
   return sat;
 }
 
