@@ -194,7 +194,7 @@ __device__ __forceinline__ void sincos_rr(float x, float* s, float* c) {
 // revolutions): the angle is reduced to a fraction of a turn in its own type,
 // then rounded to float.
 __device__ __forceinline__ void sincos_hw(double x, float* s, float* c) {
-  const float r = float(__builtin_amdgcn_fract(x * sgpr_const(0.15915494309189533577)));
+  const float r = float(__builtin_amdgcn_fract(x * kHalfAngle64[20]));
   *s = __builtin_amdgcn_sinf(r);
   *c = __builtin_amdgcn_cosf(r);
 }
