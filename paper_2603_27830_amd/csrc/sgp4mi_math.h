@@ -192,8 +192,17 @@ __device__ __forceinline__ void sincos_rr(float x, float* s, float* c) {
 
 // Hardware sine and cosine (v_sin_f32 / v_cos_f32 take the argument in
 // revolutions): the angle is reduced to a fraction of a turn in its own type,
-// then rounded to float.
+// then rounded to float.  sincos_hw keeps 1 / (2 pi) in scalar registers (read
+// from memory, as sincos_hw_mem does, the wavefront waits for it amid the secular
+// terms: 700,000 ragged tiles 366 -> 378 us).  The mixed derivatives, whose
+// results are double, use sincos_hw_mem: the compiler fuses their sums differently
+// with the other, which moves single results by a float rounding.
 __device__ __forceinline__ void sincos_hw(double x, float* s, float* c) {
+  const float r = float(__builtin_amdgcn_fract(x * sgpr_const(0.15915494309189533577)));
+  *s = __builtin_amdgcn_sinf(r);
+  *c = __builtin_amdgcn_cosf(r);
+}
+__device__ __forceinline__ void sincos_hw_mem(double x, float* s, float* c) {
   const float r = float(__builtin_amdgcn_fract(x * kHalfAngle64[20]));
   *s = __builtin_amdgcn_sinf(r);
   *c = __builtin_amdgcn_cosf(r);

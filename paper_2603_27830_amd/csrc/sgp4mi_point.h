@@ -333,10 +333,11 @@ __device__ __forceinline__ void rotate_node64(double* su, double* cu, double du,
 // 1 / (1 - ecE), 1 / (1 + betal) and 1 / (1 - e^2).  FP64 is bound by vector
 // instructions (95 % of the cycles at 100,000 satellites x 1008 times): with
 // those, the folded short-period coefficients, the one-step Kepler solution, the
-// shorter rotations, the table index without a conversion and the series in eL^2 a
-// point takes about 305 of them, and that grid 1,340 us instead of 1,679.  In float
-// the one-step solution, the series and the shorter rotations took 9,341 x 1,000
-// mixed from 72.5 to 69.5 us.
+// shorter rotations, the table index without a conversion and the series in eL^2
+// a point of 9,341 x 1,000 takes 323 of them instead of 435, and 100,000 x 1008
+// 1,317 us instead of 1,667.  In float the one-step solution, the series and the
+// shorter rotations leave 203 of 225: 9,341 x 1,000 mixed 66.0 -> 62.7 us with its
+// initialisation.
 template <class TS, class TP>
 __device__ __forceinline__ uint32_t sgp4_tail(const Grav& g, TP a, TP e, TS M, TS argp, TS node,
                                               const Incl<TS, TP>& q, PointState<TP>& out) {

@@ -20,6 +20,12 @@
 
 namespace sgp4mi {
 
+// Sines and cosines of the mixed derivatives (see sincos_hw_mem).
+struct TrigMixed {
+  static __device__ __forceinline__ void sc(double x, float* s, float* c) { sincos_hw_mem(x, s, c); }
+  static __device__ __forceinline__ void sc_damped(double x, float* s, float* c) { sincos_hw_mem(x, s, c); }
+};
+
 constexpr int kVjpBlock = 256;
 constexpr int kVjpWaves = kVjpBlock / 64;
 // Satellites per group at most: 7 x 8 lanes of one wavefront run the VJP's
@@ -72,7 +78,7 @@ __device__ __forceinline__ void wave_sum(double* acc, int lane) {
 template <class TS, class TP>
 __device__ __forceinline__ uint32_t point_vjp(const SatC<TS, TP>& c, const Grav& g, double t_abs, const TP gr[3],
                                           const TP gv[3], double* cb) {
-  using TR = Trig<TS, TP>;
+  using TR = TrigMixed;
   if (c.info & kInfoCodeMask) return c.info & kInfoCodeMask;
   if (c.info & kInfoDeep) return 7;  // deep space: not differentiated
   const bool simp = (c.info & kInfoIsimp) != 0;
@@ -653,7 +659,7 @@ __device__ __forceinline__ Tan7<TO, D> tcast(const Tan7<TI, D>& u) {
 template <class TS, class TP, class D>
 __device__ __forceinline__ uint32_t point_jvp(const SatC<TS, TP>& c, const Grav& g, double t_abs,
                                               const double (*dc)[kNRec], Tan7<TP, D> jr[3], Tan7<TP, D> jv[3]) {
-  using TR = Trig<TS, TP>;
+  using TR = TrigMixed;
   if (c.info & kInfoCodeMask) return c.info & kInfoCodeMask;
   if (c.info & kInfoDeep) return 7;  // deep space: not differentiated
   const bool simp = (c.info & kInfoIsimp) != 0;
