@@ -170,9 +170,6 @@ constexpr double kPi = 3.14159265358979323846;
 constexpr double kTwoPi = 6.28318530717958647692;
 constexpr double kInvTwoPi = 0.15915494309189533577;
 
-// x - 2*pi*round(x / 2*pi): a representative of x mod 2*pi in about [-pi, pi].
-__device__ __forceinline__ double wrap_pi(double x) { return fma(-kTwoPi, rint(x * kInvTwoPi), x); }
-
 // Non-temporal stores: outputs are written once and never re-read by the kernel.
 template <class T>
 __device__ __forceinline__ void st_nt(T* p, T x) { __builtin_nontemporal_store(x, p); }

@@ -67,18 +67,16 @@ struct Point64 {
 __device__ __forceinline__ uint32_t point64_secular(const double* c, double t_abs, Point64& p, double* U) {
   const double t = t_abs - c[kEpochMin];
   p.t = t;
-  double Mdf = fma(c[kMdot], t, c[kM0]);
-  if (fabs(t) > kFarMin) Mdf = wrap_pi(Mdf);
-  sincos_rr(Mdf, &p.sMdf, &p.cMdf);
+  const double Mdf = fma(c[kMdot], t, c[kM0]);
+  sincos_any(Mdf, &p.sMdf, &p.cMdf);
   p.x = fma(c[kEta], p.cMdf, 1.0);
   p.x3 = p.x * p.x * p.x - c[kDM0];
   const double dMa = fma(c[kMcof], p.x3, c[kArgpcof] * t);
-  double M = Mdf + dMa;
-  double argp = fma(c[kArgpdot], t, c[kArgp0]) - dMa;
-  if (fabs(t) > kFarMin) argp = wrap_pi(argp);
+  const double M = Mdf + dMa;
+  const double argp = fma(c[kArgpdot], t, c[kArgp0]) - dMa;
   double sM = p.sMdf;
   p.cM = p.cMdf;
-  if (fabs(dMa) > kRotMax) sincos_rr(M, &sM, &p.cM);
+  if (fabs(dMa) > kRotMax) sincos_any(M, &sM, &p.cM);
   else rotate_small(&sM, &p.cM, dMa);
   p.dsM = sM - c[kSinM0];
   p.A = fma(-t, fma(t, fma(t, fma(t, c[kD4], c[kD3]), c[kD2]), c[kC1]), 1.0);
@@ -90,7 +88,7 @@ __device__ __forceinline__ uint32_t point64_secular(const double* c, double t_ab
   p.clamped = e < 1.0e-6;
   e = fmax(e, 1.0e-6);
   p.e = e;
-  sincos_rr(argp, &p.sw, &p.cw);
+  sincos_any(argp, &p.sw, &p.cw);
   const double ra = rsq(a);
   p.ia = ra * ra;
   const double ax = e * p.cw;
@@ -109,7 +107,9 @@ __device__ __forceinline__ uint32_t point64_orbit(const double* c, const Grav& g
   const double a = p.a, ax = p.ax, ay = p.ay, ra = p.ra;
   double sp, cp;
   const double eb = fabs(ax) + fabs(ay);
-  const bool small = __all(eb <= kepler_small<double>());
+  bool in = eb <= kepler_small<double>();
+  in = in & (fabs(U) <= kTableMax);
+  const bool small = __all(in);
   const double iD0 = kepler64(U, ax, ay, eb, small, &sp, &cp);
   p.sp = sp;
   p.cp = cp;
@@ -145,14 +145,14 @@ __device__ __forceinline__ uint32_t point64_orbit(const double* c, const Grav& g
   const double du = -0.25 * p.k2 * c[kX7] * p.s2;
   const double kc = 1.5 * p.k2 * c[kCosi];
   const double dinc = kc * c[kSini] * p.c2;
+  double dnode = kc * p.s2;
   p.ssu = p.sinu;
   p.csu = p.cosu;
   p.sinc = c[kSini];
   p.cinc = c[kCosi];
-  rotate_node64(&p.ssu, &p.csu, du, &p.sinc, &p.cinc, dinc, c[kI0], small);
-  double node = fma(t, fma(t, c[kNodecf], c[kNodedot]), c[kNode0]);
-  if (fabs(t) > kFarMin) node = wrap_pi(node);
-  sincos_rr(node + kc * p.s2, &p.snod, &p.cnod);
+  rotate_node64(&p.ssu, &p.csu, du, &p.sinc, &p.cinc, dinc, &dnode, c[kI0], small);
+  const double node = fma(t, fma(t, c[kNodecf], c[kNodedot]), c[kNode0]);
+  sincos_any(node + dnode, &p.snod, &p.cnod);
   return p.mrt < 1.0 ? 6u : 0u;
 }
 

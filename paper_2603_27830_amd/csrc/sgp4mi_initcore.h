@@ -22,8 +22,6 @@ namespace sgp4mi {
 // Forward-mode dual number with one tangent (value, derivative).  Kept in its
 // own namespace so its math overloads are found by argument-dependent lookup
 // only and never hide the double versions.
-// An angle whose size sincos_rr takes.
-__device__ __forceinline__ double reduced(double x) { return ::fabs(x) > 1.0e12 ? wrap_pi(x) : x; }
 namespace dual {
 struct Dual1 {
   double v, d;
@@ -54,7 +52,7 @@ __device__ __forceinline__ Dual1 operator/(double a, Dual1 b) {
 __device__ __forceinline__ Dual1 fabs(Dual1 x) { return x.v < 0 ? -x : x; }
 __device__ __forceinline__ void sin_cos(Dual1 x, Dual1* s, Dual1* c) {
   double sv, cv;
-  sincos_rr(reduced(x.v), &sv, &cv);
+  sincos_any(x.v, &sv, &cv);
   *s = Dual1(sv, cv * x.d);
   *c = Dual1(cv, -sv * x.d);
 }
@@ -65,7 +63,7 @@ __device__ __forceinline__ double value(double x) { return x; }
 using dual::value;
 // Sine and cosine of an element angle: the reduced-range series of the
 // propagation kernels (any argument, no quadrant logic, no library branches).
-__device__ __forceinline__ void sin_cos(double x, double* s, double* c) { sincos_rr(reduced(x), s, c); }
+__device__ __forceinline__ void sin_cos(double x, double* s, double* c) { sincos_any(x, s, c); }
 using dual::sin_cos;
 // Reciprocal, reciprocal square root and x^(-2/3) of plain and dual numbers (a
 // shorter chain than the correctly rounded division and root); the derivatives

@@ -148,8 +148,21 @@ __device__ __forceinline__ double sgpr_const(double x) {
 // cos b through b^6 (the next terms are below 4e-19 and 3.3e-18 relative),
 // combined by angle addition.  n is rounded by adding 1.5 * 2^52 + 64: the low
 // bits of the sum are n + 64, so the table index takes no conversion, and the
-// mask keeps it inside the table for every input (NaN, infinity, huge).  Angles
-// beyond 1e14, whose spacing exceeds pi / 128, must be reduced before.
+// mask keeps it inside the table for every input (NaN, infinity, huge).  The sum
+// holds n to a whole number up to |x| = 1.1e14; larger angles (elements of that
+// size, or the drag polynomials long after a decay) must first be reduced by
+// whole turns (reduced: in two parts, which leaves them below that up to 1e29).
+// The propagation checks its angles together (a check in each sine cost 6 % at
+// 100,000 x 1008 FP64); sincos_any checks its own.
+constexpr double kTableMax = 0x1p46;
+__device__ __forceinline__ double reduced(double x) {
+  if (fabs(x) > kTableMax) {
+    const double turns = rint(x * 0.15915494309189533577);
+    x = fma(-turns, 6.2831853071795864769, x);  // 2 pi, nearest double
+    x = fma(-turns, 2.4492935982947063e-16, x);  // 2 pi minus that
+  }
+  return x;
+}
 __device__ __forceinline__ void sincos_rr(double x, double* s, double* c) {
   const double round64 = 6755399441055808.0;       // 1.5 * 2^52 + 64
   const double m = fma(x, sgpr_const(20.371832715762604), round64);  // 64 / pi
@@ -182,6 +195,8 @@ __device__ __forceinline__ void sincos_rr(double x, double* s, double* c) {
   *s = fma(ca, sb, fma(sa, q, sa));
   *c = fma(-sa, sb, fma(ca, q, ca));
 }
+
+__device__ __forceinline__ void sincos_any(double x, double* s, double* c) { sincos_rr(reduced(x), s, c); }
 
 __device__ __forceinline__ void sincos_rr(float x, float* s, float* c) {
   const float n = rintf(x * 0.15915494309189533577f);

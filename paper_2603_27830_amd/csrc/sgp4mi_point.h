@@ -151,10 +151,6 @@ struct Trig<double, float> {
   static __device__ __forceinline__ void sc_damped(double x, float* s, float* c) { sincos_hw(x, s, c); }
 };
 
-__device__ __forceinline__ double wrap(double x) { return wrap_pi(x); }
-__device__ __forceinline__ float wrap(float x) {
-  return fmaf(-6.28318530717958647692f, rintf(x * 0.15915494309189533577f), x);
-}
 __device__ __forceinline__ double sq_root(double x) { return sqrt(x); }
 __device__ __forceinline__ float sq_root(float x) { return __builtin_amdgcn_sqrtf(x); }
 // a + b t for per-satellite constants a and b.  Double keeps the product and
@@ -245,16 +241,13 @@ struct Incl {
   TP A1, X1h, X1k, X7q, CN, CI;
 };
 
-// Times this far from epoch (minutes) have their secular angles reduced before
-// sincos_rr, which takes angles up to 1e14.
-constexpr double kFarMin = 1.0e12;
-
 // FP64: sin and cos of the eccentric longitude psi, and an estimate (relative
 // error below 1e-5) of 1 / (1 - axn cos psi - ayn sin psi).
 //
-// Where eb = |axn| + |ayn| is at most kepler_small in every lane (small) the
-// wavefront takes one step instead of Newton's two: with s = f / f' at psi = U, S = axn sin U - ayn cos U, C = axn
-// cos U + ayn sin U and c = C / f', the offset solves
+// Where eb = |axn| + |ayn| is at most kepler_small and U in the sine table's range
+// in every lane (small) the wavefront takes one step instead of Newton's two:
+// with s = f / f' at psi = U, S = axn sin U - ayn cos U, C = axn cos U + ayn sin U
+// and c = C / f', the offset solves
 //   d = s - (s / 2) d^2 - (c / 6) d^3 + (s / 24) d^4 + ...,
 // d = s - s^3 (1/2 + c/6) + (13/24) s^5 up to 0.43 c s^5 (3e-16 at the bound;
 // Newton ends with up to 5e-13).  At 100,000 x 1008 over a week the second
@@ -265,10 +258,9 @@ template <> __device__ __forceinline__ constexpr double kepler_small<double>() {
 template <> __device__ __forceinline__ constexpr float kepler_small<float>() { return 4.5e-3f; }
 __device__ __forceinline__ double kepler64(double U, double axn, double ayn, double eb, bool small, double* sp_,
                                            double* cp_) {
-  double sp, cp;
-  sincos_rr(U, &sp, &cp);
-  double iD;
+  double sp, cp, iD;
   if (small) {
+    sincos_rr(U, &sp, &cp);
     const double S = axn * sp - ayn * cp, C = axn * cp + ayn * sp;
     const double D = 1.0 - C;
     iD = __builtin_amdgcn_rcp(D);
@@ -278,6 +270,8 @@ __device__ __forceinline__ double kepler64(double U, double axn, double ayn, dou
     p = fma(w, sgpr_const(5.41666666666666666667e-1), p);
     rotate_mid(&sp, &cp, fma(s * w, p, s));
   } else {
+    U = reduced(U);
+    sincos_rr(U, &sp, &cp);
     double dpsi = 0.0;
     const KeplerExit<double> done(eb);
     for (int k = 0; k < 10; ++k) {
@@ -298,22 +292,24 @@ __device__ __forceinline__ double kepler64(double U, double axn, double ayn, dou
 // FP64: (sin u, cos u), a unit vector up to rounding, turned by du, and (sin i0,
 // cos i0) by dinc.  One Newton step from 1 normalises the first pair to
 // O(delta^2), delta = |.|^2 - 1.  Orbits above the Earth's surface stay within
-// kRotTiny (|du| <= 8.2e-4 / p_L^2, |dinc| <= 4.1e-4 / p_L^2).
+// kRotTiny (|du|, |dnode| <= 8.2e-4 / p_L^2, |dinc| <= 4.1e-4 / p_L^2).  A dnode
+// beyond the sine table's range (p_L far below that) is reduced.
 __device__ __forceinline__ void rotate_node64(double* su, double* cu, double du, double* si, double* ci, double dinc,
-                                              double i0, bool small) {
+                                              double* dnode, double i0, bool small) {
   const double sinu = *su, cosu = *cu;
   const double n2 = sinu * sinu + cosu * cosu;
   double h = fma(n2, -0.5, 1.5);
   if (!small && fabs(n2 - 1.0) > 1.0e-8) h = rsq(n2);  // (small eccentricities: rounding alone)
   double s = sinu * h, c = cosu * h;
-  if (fmax(fabs(du), fabs(dinc)) <= kRotTiny) {
+  if (fmax(fmax(fabs(du), fabs(*dnode)), fabs(dinc)) <= kRotTiny) {
     rotate_tiny(&s, &c, du);
     rotate_tiny(si, ci, dinc);
   } else {
     if (fabs(du) <= kRotMax) rotate_small(&s, &c, du);
-    else sincos_rr(arctan2(sinu, cosu) + du, &s, &c);
+    else sincos_any(arctan2(sinu, cosu) + du, &s, &c);
     if (fabs(dinc) <= kRotMax) rotate_small(si, ci, dinc);
-    else sincos_rr(i0 + dinc, si, ci);
+    else sincos_any(i0 + dinc, si, ci);
+    *dnode = reduced(*dnode);
   }
   *su = s;
   *cu = c;
@@ -370,7 +366,9 @@ __device__ __forceinline__ uint32_t sgp4_tail(const Grav& g, TP a, TP e, TS M, T
   // long-period correction L_T = L + tau L_cof a_xN: node cancels.
   const TS U = M + argp + TS(tau * q.Lcof * axn);
   const TP eb = vabs(axn) + vabs(ayn);
-  const bool small = __all(eb <= kepler_small<TP>());
+  bool in = eb <= kepler_small<TP>();
+  if constexpr (kDouble) in = in & (vabs(U) <= kTableMax);
+  const bool small = __all(in);
   TP sp, cp, iD0;
   if constexpr (kDouble) {
     iD0 = kepler64(U, axn, ayn, eb, small, &sp, &cp);
@@ -444,7 +442,7 @@ __device__ __forceinline__ uint32_t sgp4_tail(const Grav& g, TP a, TP e, TS M, T
   const TP s2 = ip2 * sin2u, c2 = ip2 * cos2u;
   const TP mrt = rl * vfma(-ip2 * betal, q.A1, TP(1)) + inv_pl * cos2u * q.X1h;
   const TP du = q.X7q * s2;
-  const TP dnode = q.CN * s2;
+  TP dnode = q.CN * s2;
   const TP dinc = q.CI * c2;
   const TP mvt = rdotl - ni * sin2u * q.X1k;
   const TP rvdot = rvdotl + ni * vfma(q.X1k, cos2u, q.A1);
@@ -452,7 +450,7 @@ __device__ __forceinline__ uint32_t sgp4_tail(const Grav& g, TP a, TP e, TS M, T
   // Orientation: sin/cos of u_k = u + du, i_k = i0 + dinc, node_k = node + dnode.
   TP ssu = sinu, csu = cosu, sinc = q.sini, cinc = q.cosi;
   if constexpr (kDouble) {
-    rotate_node64(&ssu, &csu, du, &sinc, &cinc, dinc, q.i0, small);
+    rotate_node64(&ssu, &csu, du, &sinc, &cinc, dinc, &dnode, q.i0, small);
   } else {
     // (sinu, cosu) is a unit vector up to rounding (~1e-6 at most): one Newton
     // step from 1 normalises it
@@ -653,10 +651,10 @@ __device__ __forceinline__ uint32_t deep_point(const SatC<TS, TP>& c, const Grav
     argp = argp - twopi * floor(argp * itwopi);
     L = L - twopi * floor(L * itwopi);
     M = L - argp - node;
-  } else if (vabs(t) > TS(kFarMin)) {
-    M = wrap(M);
-    argp = wrap(argp);
-    node = wrap(node);
+  } else if (vmax(vmax(vabs(M), vabs(argp)), vabs(node)) > kTableMax) {
+    M = reduced(M);
+    argp = reduced(argp);
+    node = reduced(node);
   }
   // lunar and solar long-period terms
   TS pe = TS(0), pinc = TS(0), pl = TS(0), pgh = TS(0), ph = TS(0);
@@ -664,10 +662,10 @@ __device__ __forceinline__ uint32_t deep_point(const SatC<TS, TP>& c, const Grav
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
     const double* q = d + kDPer0 + kNPer * k;
-    TS Mb = TS(d[kDMb0 + k]) + TS(nb[k]) * t;
-    if (sizeof(TS) == 8 && vabs(t) > TS(kFarMin)) Mb = wrap(Mb);
+    const TS Mb = TS(d[kDMb0 + k]) + TS(nb[k]) * t;
     TS sf, cf;
-    Trig<TS, TS>::sc(Mb, &sf, &cf);
+    if constexpr (sizeof(TS) == 8) sincos_any(Mb, &sf, &cf);
+    else Trig<TS, TS>::sc(Mb, &sf, &cf);
     const TS df = TS(2.0 * eb[k]) * sf;
     // double: a rotation (the series' next terms are below 7e-15 at 0.11, on
     // terms of 1e-2 at most)
@@ -686,7 +684,8 @@ __device__ __forceinline__ uint32_t deep_point(const SatC<TS, TP>& c, const Grav
   TS incp = incl + pinc;
   e = e + pe;
   TS si, ci;
-  Trig<TS, TS>::sc(incp, &si, &ci);
+  if constexpr (sizeof(TS) == 8) sincos_any(incp, &si, &ci);
+  else Trig<TS, TS>::sc(incp, &si, &ci);
   if (incp >= TS(0.2)) {
     if constexpr (sizeof(TS) == 8) ph = ph * rcp(si);
     else ph = ph / si;
@@ -778,11 +777,13 @@ __device__ __forceinline__ uint32_t sgp4_point(const SatC<TS, TP>& c, const Grav
     if (!(e_s >= TP(-0.001) && e_s < TP(1))) return 1;
     M = M + c.n0pp * (Ld * t2);
   } else {
-    // FP64: sin M from sin/cos of the drag-free M by a small rotation
-    if (vabs(t) > TS(kFarMin)) {
-      Mdf = wrap(Mdf);
-      argpdf = wrap(argpdf);
-      node = wrap(node);
+    // FP64: sin M from sin/cos of the drag-free M by a small rotation.  Angles
+    // beyond the sine table's range are reduced: the secular ones here, those
+    // that the drag terms drive there where those are large, U by Kepler's step.
+    if (vmax(vmax(vabs(Mdf), vabs(argpdf)), vabs(node)) > kTableMax) {
+      Mdf = reduced(Mdf);
+      argpdf = reduced(argpdf);
+      node = reduced(node);
       M = Mdf;
       argp = argpdf;
     }
@@ -799,8 +800,13 @@ __device__ __forceinline__ uint32_t sgp4_point(const SatC<TS, TP>& c, const Grav
       argp = argpdf - dMa;
       const TS t3 = t2 * t, t4 = t3 * t;
       A = A - c.D2 * t2 - c.D3 * t3 - c.D4 * t4;
-      if (vabs(dMa) > TS(kRotMax)) TR::sc_damped(M, &sM, &cM);
-      else rotate_small(&sM, &cM, TP(dMa));
+      if (vabs(dMa) > TS(kRotMax)) {
+        M = reduced(M);
+        argp = reduced(argp);
+        TR::sc_damped(M, &sM, &cM);
+      } else {
+        rotate_small(&sM, &cM, TP(dMa));
+      }
       Ed = Ed + c.bC5 * TS(sM - c.sinM0);
       Ld = Ld + c.t3cof * t3 + t4 * lin(c.t4cof, c.t5cof, t);
     }
