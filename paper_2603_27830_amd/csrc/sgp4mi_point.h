@@ -414,7 +414,7 @@ __device__ __forceinline__ uint32_t sgp4_tail(const Grav& g, TP a, TP e, TS M, T
     }
   } else {
     const TP om = TP(1) - eL2;
-    if (!(om >= TP(0))) return 4;  // a > 0 here
+    if (!(om >= TP(0))) return 4;  // a >= 0: a0 A^2, in float a0 + a0 q with q = dA (dA - 2) >= -1
     if constexpr (kDouble) {
       const TP rb = rsq(om);
       betal = om * rb;

@@ -744,10 +744,17 @@ static hipError_t screen_global(const TR* r, const uint8_t* err, int64_t n, int6
   return hipGetLastError();
 }
 
+// Catalogues beyond this take the device-memory path: every column set streams
+// the whole time's class bytes, which grows with the square of n, and a class
+// byte numbers up to 127 sets (0x7f is left to invalid points).
+constexpr int64_t kSlabMaxN = 200000;
+
 // Workspace of the two paths: the larger one's, the device-memory path's (the
-// header, the per-time bucket offsets and 12 bytes per point).
+// header, the per-time bucket offsets and 12 bytes per point).  The column path
+// counts where it can be taken only: beyond four million satellites, where the
+// buckets stop growing, its layout would be the larger one.
 size_t screen_ws_bytes(int64_t n, int64_t T) {
-  const size_t slab = slab_ws_bytes(n, T);
+  const size_t slab = n <= kSlabMaxN ? slab_ws_bytes(n, T) : 0;
   const size_t glob = global_ws_bytes(n, T);
   return slab > glob ? slab : glob;  // enough for either path
 }
@@ -756,11 +763,6 @@ size_t screen_ws_bytes(int64_t n, int64_t T) {
 bool screen_global_fits(int64_t n, int64_t T) {
   return n <= 0x7fffffff && n * T <= int64_t(0x7fffffff) * 256 && T <= 0x7fffffff;
 }
-
-// Catalogues beyond this take the device-memory path: every column set streams
-// the whole time's class bytes, which grows with the square of n, and a class
-// byte numbers up to 127 sets (0x7f is left to invalid points).
-constexpr int64_t kSlabMaxN = 200000;
 
 // Column sets per time: a table has room for 30% more than a set's even share,
 // and a further quarter per 100,000 satellites, since the sets then have few
