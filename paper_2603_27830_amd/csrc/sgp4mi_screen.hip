@@ -139,6 +139,11 @@ __device__ __forceinline__ uint32_t block_of(int32_t column, int32_t left, float
   return uint32_t((float(column - left) + 0.5f) * inv_width);
 }
 
+// A finite double beyond float's range as float's largest (its points only meet
+// each other, and the exact test decides on the stored positions).
+__device__ __forceinline__ float in_float(float z) { return z; }
+__device__ __forceinline__ float in_float(double z) { return float(fmin(fmax(z, -3.4028234663852886e38), 3.4028234663852886e38)); }
+
 // Pack one 64 x 64 tile.  A lane has its 48 position loads (16 points) out
 // before it uses one: 9,341 x 1,000 floats 54 us for three coordinates, against
 // 60 for two when each point's loads were waited for in turn.
@@ -164,8 +169,8 @@ __global__ void __launch_bounds__(256) screen_pack(const TR* __restrict__ r, con
   float most = 0.0f;
 #pragma unroll
   for (int q = 0; q < 16; ++q) {
-    const float x = float(c[0][q]), y = float(c[1][q]), z = float(c[2][q]);
-    const bool ok = isfinite(x) && isfinite(y) && isfinite(z) && (code[q] == 0 || code[q] == 6);
+    const float x = float(c[0][q]), y = float(c[1][q]), z = in_float(c[2][q]);
+    const bool ok = isfinite(x) && isfinite(y) && isfinite(double(c[2][q])) && (code[q] == 0 || code[q] == 6);
     if (ok) most = fmaxf(most, fmaxf(fabsf(x), fmaxf(fabsf(y), fabsf(z))));
     else c[0][q] = TR(__builtin_inff());
   }
@@ -176,7 +181,7 @@ __global__ void __launch_bounds__(256) screen_pack(const TR* __restrict__ r, con
     float* const out = d == 0 ? L.x : d == 1 ? L.y : L.z;
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < 16; ++q) tile[wave + 4 * q][lane] = float(c[d][q]);
+    for (int q = 0; q < 16; ++q) tile[wave + 4 * q][lane] = d == 2 ? in_float(c[d][q]) : float(c[d][q]);
     __syncthreads();
     const int64_t i = i0 + lane;  // consecutive lanes: consecutive satellites at one time
 #pragma unroll
