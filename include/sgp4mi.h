@@ -187,7 +187,7 @@ int sgp4_propagate_elements_ex(const double* grav, const double* ref_jd, int64_t
  * Up to 200,000 satellites, each time's valid points are hashed by (x, y) cells
  * at least D wide in on-chip memory, by sets of x columns for more than 3,072
  * satellites, and every point is tested against the cells around it (clearing,
- * packing and sweep kernels; two more for several column sets); larger batches
+ * packing and sweep kernels; one more for several column sets); larger batches
  * sort buckets of x in ws (a range reduction, a histogram, a scan per time, a
  * placement and a sweep).
  * dist_km finite and > 0 (else SGP4_E_ARG); n * T within 2^31 * 256 (else

@@ -43,23 +43,23 @@ __device__ __forceinline__ double dist2(const TR* __restrict__ r, int64_t P, int
 }
 
 // ---------------------------------------------------------- column path --
-// Workspace: the cells per slot of sample times, a class byte per point (rows
-// of T, each padded to whole words), then x, y and z as [T][n] floats.
+// Workspace: a slot per sixteen time tiles, a class byte per point (rows of T,
+// each padded to whole words), then x, y and z as [T][n] floats.
 constexpr int kSlots = 16;
-// Cells of the sample times of one slot (time tiles of 64 in turn).  near: the
-// float distance in one axis of any pair closer than D; reach: the column width,
-// which also covers the roundings of a coordinate times its reciprocal (2^-24
-// of up to R / w each).  Before slab_geometry, near holds the bits of the
-// largest coordinate R (non-negative floats order as integers).
-struct SlabCells {
-  float near, reach;
-  int32_t left;   // leftmost column
-  int32_t width;  // columns per block
+// What the sample times of one slot (time tiles of 64 in turn) share: the bits of
+// the largest |x| or |y| and of the largest |z| (non-negative floats order as
+// integers), and the height of the rows in column widths.
+struct SlabSlot {
+  uint32_t rxy, rz;
+  uint32_t rows;  // float bits
+  uint32_t pad;
 };
-static_assert(kSlots * sizeof(SlabCells) == 256, "the workspace's first 256 bytes");
+static_assert(kSlots * sizeof(SlabSlot) == 256, "the workspace's first 256 bytes");
+
+constexpr float kRowsMax = 16.0f;
 
 struct SlabLayout {
-  SlabCells* cells;
+  SlabSlot* slots;
   uint32_t* cls;  // [T][words]
   float *x, *y, *z;
   int64_t words;
@@ -70,8 +70,8 @@ __device__ __forceinline__ int slot_of(int64_t k) { return int((k >> 6) & (kSlot
 static SlabLayout slab_layout(void* ws, int64_t n, int64_t T) {
   SlabLayout L;
   L.words = (n + 3) / 4;
-  L.cells = static_cast<SlabCells*>(ws);
-  L.cls = reinterpret_cast<uint32_t*>(L.cells + kSlots);
+  L.slots = static_cast<SlabSlot*>(ws);
+  L.cls = reinterpret_cast<uint32_t*>(L.slots + kSlots);
   L.x = reinterpret_cast<float*>(L.cls + L.words * T);
   L.y = L.x + n * T;
   L.z = L.y + n * T;
@@ -80,64 +80,42 @@ static SlabLayout slab_layout(void* ws, int64_t n, int64_t T) {
 
 // 13 bytes a point and a little: within the device-memory path's workspace.
 static size_t slab_ws_bytes(int64_t n, int64_t T) {
-  return sizeof(SlabCells) * kSlots + 4 * (size_t((n + 3) / 4) * size_t(T) + 3 * size_t(n) * size_t(T));
+  return sizeof(SlabSlot) * kSlots + 4 * (size_t((n + 3) / 4) * size_t(T) + 3 * size_t(n) * size_t(T));
 }
 
 __global__ void __launch_bounds__(64) slab_clear(SlabLayout L, unsigned long long* count) {
   if (threadIdx.x == 0) *count = 0ull;
-  if (threadIdx.x < kSlots) L.cells[threadIdx.x].near = 0.0f;
+  if (threadIdx.x < kSlots) L.slots[threadIdx.x] = SlabSlot{0u, 0u, __float_as_uint(kRowsMax), 0u};
 }
 
-// Rows (cells along y) are this many column widths tall.  A point looks up its
-// own cell, the one above when it is within reach, and one or two of the next
-// column: tall rows mean fewer lookups, but a cell should rarely hold a point
-// (spread over a sphere, a cell of w by h w holds about 0.6 n h (w / R)^2; the
-// factor aims at 0.15).  Below two widths a point could reach both neighbours.
-__device__ __forceinline__ float row_widths(const SlabCells& c, int32_t n) {
-  const float l = float(c.left);
-  return fminf(fmaxf(0.25f * l * l / float(n), 2.5f), 16.0f);
-}
-
-// A block is `width` columns and belongs to set (block number) mod slabs.  Several
-// blocks per set meet the range of x at equal distances, which evens the sets
-// out for a smooth distribution; but whole columns, a last incomplete round of
-// blocks and the columns next to the blocks weigh the more the narrower they
-// are.  Taken: the width that leaves the fullest set the fewest columns, one
-// block per set counted a sixth more and two a twelfth.
-__device__ __forceinline__ SlabCells cells_of(float R, double D) {
-  SlabCells c;
-  c.near = float((D + 2.4e-7 * double(R)) * (1.0 + 1.0e-6));
-  c.reach = float((D + 8.0e-7 * double(R)) * (1.0 + 1.0e-5));
-  c.left = -int32_t(floorf(R * (1.0f / c.reach))) - 1;
-  c.width = 1;
+// Cells of a slot's times.  near, near_z: the float distance along x or y, and
+// along z, of any pair closer than D; reach: the column width, which also covers
+// the roundings of a coordinate times its reciprocal (2^-24 of up to R / w each).
+struct Cells {
+  float near, near_z, reach, inv_w;
+};
+__device__ __forceinline__ Cells cells_of(const SlabSlot& s, double D) {
+  const double R = double(__uint_as_float(s.rxy)), Rz = double(__uint_as_float(s.rz));
+  Cells c;
+  c.near = float((D + 2.4e-7 * R) * (1.0 + 1.0e-6));
+  c.near_z = float((D + 2.4e-7 * Rz) * (1.0 + 1.0e-6));
+  c.reach = float((D + 8.0e-7 * R) * (1.0 + 1.0e-5));
+  c.inv_w = 1.0f / c.reach;
   return c;
 }
 
-__global__ void __launch_bounds__(64) slab_geometry(SlabLayout L, double D, int32_t slabs) {
-  if (threadIdx.x >= kSlots) return;
-  SlabCells c = cells_of(L.cells[threadIdx.x].near, D);
-  const uint32_t columns = uint32_t(-2 * c.left);
-  uint32_t best = 0xffffffffu;
-  for (uint32_t m = 1; m <= 6; ++m) {
-    const uint32_t width = (columns + m * slabs - 1) / (m * slabs);
-    const uint32_t blocks = (columns + width - 1) / width;
-    const uint32_t fullest = (blocks + slabs - 1) / slabs * (width + 1) * (m == 1 ? 14 : m == 2 ? 13 : 12);
-    if (fullest < best) {
-      best = fullest;
-      c.width = int32_t(width);
-    }
-  }
-  L.cells[threadIdx.x] = c;
+// Rows (cells along y) are this many column widths tall, for n points spread over
+// a sphere of l columns radius.  A point looks up its own cell, the one above when
+// it is within reach, and one or two of the next column: tall rows mean fewer
+// lookups, but a cell should rarely hold a point (it holds about 0.6 n h / l^2 on
+// average; the factor aims at 0.15).  Below two widths a point could reach both
+// neighbours.
+__device__ __forceinline__ float row_widths(float l, float n) {
+  return fminf(fmaxf(0.25f * l * l / n, 2.5f), kRowsMax);
 }
 
-// Column of x and block of a column (both from the left end of the range, so
-// non-negative for every valid point; below 2.7 million, where the quotient by
-// the float reciprocal of the width is exact: the half keeps it 0.5 / width away
-// from whole numbers).
+// Column of x: below 1.3 million in size for every valid point.
 __device__ __forceinline__ int32_t column_of(float x, float inv_w) { return int32_t(floorf(x * inv_w)); }
-__device__ __forceinline__ uint32_t block_of(int32_t column, int32_t left, float inv_width) {
-  return uint32_t((float(column - left) + 0.5f) * inv_width);
-}
 
 // A finite double beyond float's range as float's largest (its points only meet
 // each other, and the exact test decides on the stored positions).
@@ -151,7 +129,7 @@ template <class TR>
 __global__ void __launch_bounds__(256) screen_pack(const TR* __restrict__ r, const uint8_t* __restrict__ err, int64_t n,
                                                    int64_t T, SlabLayout L) {
   __shared__ float tile[64][65];
-  __shared__ float wave_max[4];
+  __shared__ float wave_max[2][4];
   const int64_t k0 = int64_t(blockIdx.x) * 64, i0 = int64_t(blockIdx.y) * 64;  // times on x: T may be large
   const int64_t P = n * T;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -166,16 +144,26 @@ __global__ void __launch_bounds__(256) screen_pack(const TR* __restrict__ r, con
     for (int d = 0; d < 3; ++d) c[d][q] = in ? r[d * P + p] : TR(0);
     code[q] = in && err ? err[p] : uint8_t(0);
   }
-  float most = 0.0f;
+  float most = 0.0f, most_z = 0.0f;
 #pragma unroll
   for (int q = 0; q < 16; ++q) {
     const float x = float(c[0][q]), y = float(c[1][q]), z = in_float(c[2][q]);
     const bool ok = isfinite(x) && isfinite(y) && isfinite(double(c[2][q])) && (code[q] == 0 || code[q] == 6);
-    if (ok) most = fmaxf(most, fmaxf(fabsf(x), fmaxf(fabsf(y), fabsf(z))));
-    else c[0][q] = TR(__builtin_inff());
+    if (ok) {
+      most = fmaxf(most, fmaxf(fabsf(x), fabsf(y)));
+      most_z = fmaxf(most_z, fabsf(z));
+    } else {
+      c[0][q] = TR(__builtin_inff());
+    }
   }
-  for (int o = 32; o > 0; o >>= 1) most = fmaxf(most, __shfl_xor(most, o));
-  if (lane == 0) wave_max[wave] = most;
+  for (int o = 32; o > 0; o >>= 1) {
+    most = fmaxf(most, __shfl_xor(most, o));
+    most_z = fmaxf(most_z, __shfl_xor(most_z, o));
+  }
+  if (lane == 0) {
+    wave_max[0][wave] = most;
+    wave_max[1][wave] = most_z;
+  }
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
     float* const out = d == 0 ? L.x : d == 1 ? L.y : L.z;
@@ -190,33 +178,196 @@ __global__ void __launch_bounds__(256) screen_pack(const TR* __restrict__ r, con
       if (i < n && k < T) out[k * n + i] = tile[lane][wave + 4 * q];
     }
   }
-  if (threadIdx.x == 0)
-    atomicMax(reinterpret_cast<uint32_t*>(&L.cells[slot_of(k0)].near),
-              __float_as_uint(fmaxf(fmaxf(wave_max[0], wave_max[1]), fmaxf(wave_max[2], wave_max[3]))));
+  if (threadIdx.x < 2) {
+    const float* const m = wave_max[threadIdx.x];
+    SlabSlot& slot = L.slots[slot_of(k0)];
+    atomicMax(threadIdx.x == 0 ? &slot.rxy : &slot.rz, __float_as_uint(fmaxf(fmaxf(m[0], m[1]), fmaxf(m[2], m[3]))));
+  }
+}
+
+// Strips of columns, in their order, fine near the origin and 1/256 of the distance
+// from it beyond 64 columns: whatever the range of x, a strip of the densest part
+// holds a small share of the points.  With v = 64 + the column's distance from the
+// origin, a strip is the leading eight bits of v's fraction at v's exponent: 256
+// strips per doubling, 15 doublings to the largest column.  Columns are taken as
+// floats here (exact below 2^23).
+constexpr int kStripShift = 23 - 8, kStrips = 8192;
+constexpr uint32_t kStripZero = 0x42800000u >> kStripShift;  // 64.0f
+__device__ __forceinline__ uint32_t strip_of(float column) {
+  const float v = fminf(fabsf(column + 0.5f) + 63.5f, 0x1p21f);
+  const uint32_t s = __float_as_uint(v) >> kStripShift;
+  return column < 0.0f ? kStrips / 2 - 1 + kStripZero - s : kStrips / 2 - kStripZero + s;
+}
+// The first column of a strip that has one.
+__device__ __forceinline__ float strip_column(uint32_t strip) {
+  const uint32_t half = kStrips / 2;
+  if (strip >= half) return ceilf(__uint_as_float((strip - half + kStripZero) << kStripShift)) - 64.0f;
+  return 64.0f - ceilf(__uint_as_float((half - strip + kStripZero) << kStripShift));
+}
+// Columns of a strip (the strips of the first two doublings are finer than a column).
+__device__ __forceinline__ float strip_columns(uint32_t strip) {
+  const uint32_t s = strip < kStrips / 2 ? kStrips / 2 - 1 - strip : strip - kStrips / 2;
+  return s < 3u << 8 ? 1.0f : float(1 << ((s >> 8) - 2));
 }
 
 // Class byte of every point: its column set and, in bit 7, whether its column is
-// the first of its block; invalid points 0xff.
-// The column sets' workgroups then test four points per instruction.
-__global__ void __launch_bounds__(256) screen_class(SlabLayout L, int32_t n, int64_t T, int32_t slabs) {
-  const int64_t per = (L.words + 255) / 256;  // workgroups per sample time
-  const int64_t k = blockIdx.x / per;
-  const int64_t word = (blockIdx.x - k * per) * 256 + threadIdx.x;
-  if (word >= L.words) return;
-  const SlabCells g = L.cells[slot_of(k)];
-  const float inv_w = 1.0f / g.reach, inv_width = 1.0f / float(g.width);
-  uint32_t out = 0;
+// the first of a run; invalid points 0xff.  The column sets' workgroups then test
+// four points per instruction.
+//
+// Runs of strips share a time's points evenly, so they follow the points and not
+// the largest coordinate (blocks of equal width over [-R, R] put 3,817 of 9,341 low
+// satellites into one of five sets when another one is at 42,164 km, and 9,340
+// when it is at 120,000 km).  A set is two runs half the range apart, since cells
+// near the limb hold more points than those at the centre; where a column holds
+// more than kTwoRunsColumn points, whose copies above each run would crowd the
+// table, it is one.  A workgroup counts its time's points by strip in LDS (beyond
+// 16,384 satellites one of each of so many stretches of them: a run's share comes
+// out within a tenth or so), numbers the strips' runs, and writes its part of the
+// class bytes.  A run begins at the strip that holds a multiple of the share in
+// its first half, or after the one that holds it in its second; only strips with
+// counted points begin one, so that the runs are numbered in the order of x
+// without gaps and the points next to a run's upper edge are the first column of
+// the next number.  The mean density around a point gives the rows' height.
+//
+// Bound by latency (a load, the counts, two sums over the workgroup) and, over many
+// times, by VALU issue: all loads are out before one is used.  9,341 x 100 13 us,
+// 100,000 x 144 43 us; the class bytes from equal blocks and their geometry took 8
+// and 27, the sweep then 21 and 523 instead of 18 and 479.
+constexpr int kSetsBlock = 1024, kSetsWaves = kSetsBlock / 64;
+constexpr int kSetSamples = 1 << 14;
+constexpr float kTwoRunsColumn = 200.0f;
+__global__ void __launch_bounds__(kSetsBlock)
+    screen_sets(SlabLayout L, int32_t n, int64_t T, double D, int32_t slabs, int32_t parts, int32_t part_words) {
+  constexpr int kOwn = kStrips / kSetsBlock, kLoads = kSetSamples / kSetsBlock;
+  static_assert(kOwn == 8 && kSetsWaves == 16, "two loads of four counts, one store of eight numbers; sums of sixteen");
+  __shared__ __align__(16) int4 count[kStrips / 4];
+  __shared__ uint64_t run_of[kStrips / 8];
+  __shared__ float run_column[256];  // a run's first column
+  __shared__ int32_t wave_points[kSetsWaves], wave_last[kSetsWaves], wave_begins[kSetsWaves];
+  __shared__ float wave_dense[kSetsWaves];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t k = blockIdx.x / parts;
+  const int32_t word0 = int32_t(blockIdx.x - k * parts) * part_words, words = int32_t(L.words);
+  const int32_t word1 = word0 + part_words < words ? word0 + part_words : words;
+  const float* const X = L.x + k * int64_t(n);
+  const float inf = __builtin_inff();
+  auto word_points = [&](int32_t word, float x[4]) {
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const int64_t i = 4 * word + e;
-    const float x = i < n ? L.x[k * n + i] : __builtin_inff();
-    const int32_t c = column_of(x, inv_w);
-    const uint32_t b = block_of(c, g.left, inv_width);
-    const uint32_t first = int32_t(b) * g.width == c - g.left ? 0x80u : 0u;
-    const uint32_t v = x < __builtin_inff() ? b % uint32_t(slabs) | first : 0xffu;
-    out |= v << (8 * e);
+    for (int e = 0; e < 4; ++e) x[e] = word < word1 && 4 * word + e < n ? X[4 * word + e] : inf;
+  };
+  float mine[4];
+  word_points(word0 + int32_t(threadIdx.x), mine);
+  const Cells g = cells_of(L.slots[slot_of(k)], D);
+  count[2 * threadIdx.x] = count[2 * threadIdx.x + 1] = make_int4(0, 0, 0, 0);
+  if (threadIdx.x == 0) run_column[0] = -inf;
+  const int32_t samples = n < kSetSamples ? n : kSetSamples;
+  float x[kLoads];
+#pragma unroll
+  for (int e = 0; e < kLoads; ++e) {
+    const uint32_t q = uint32_t(e * kSetsBlock) + threadIdx.x;
+    uint32_t i = q;
+    // beyond kSetSamples: any one of the stretch's satellites (q n < 2^32)
+    if (n > kSetSamples) i = ((q * uint32_t(n)) >> 14) + __umulhi(q * 0x9e3779b1u, uint32_t(n) >> 14);
+    x[e] = int32_t(q) < samples ? X[i] : inf;
   }
-  L.cls[k * L.words + word] = out;
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < kLoads; ++e)
+    if (x[e] < inf) atomicAdd(reinterpret_cast<int32_t*>(count) + strip_of(floorf(x[e] * g.inv_w)), 1);
+  __syncthreads();
+
+  // this lane's strips: their counts, the last count that is not zero, the points
+  // before them and the last such count before them
+  const int4 c0 = count[2 * threadIdx.x], c1 = count[2 * threadIdx.x + 1];
+  const int32_t own[kOwn] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
+  int32_t sum = 0, last = 0;
+  float dense = 0.0f;
+#pragma unroll
+  for (int e = 0; e < kOwn; ++e) {
+    sum += own[e];
+    last = own[e] > 0 ? own[e] : last;
+    dense += float(own[e]) * float(own[e] - 1);
+  }
+  dense /= strip_columns(kOwn * threadIdx.x);  // (the same for all eight)
+  auto scan = [&](int32_t v, int lanes) {
+    for (int o = 1; o < lanes; o <<= 1) {
+      const int32_t u = __shfl_up(v, o);
+      if (lane >= o) v += u;
+    }
+    return v;
+  };
+  int32_t at = scan(sum, 64);
+  const unsigned long long any = __ballot(last > 0);
+  const unsigned long long lower = any & ((1ull << lane) - 1ull);
+  int32_t prev = __shfl(last, lower ? 63 - __clzll(lower) : 0);
+  const int32_t top = __shfl(last, any ? 63 - __clzll(any) : 0);
+  for (int o = 32; o > 0; o >>= 1) dense += __shfl_xor(dense, o);
+  if (lane == 63) {
+    wave_points[wave] = at;
+    wave_last[wave] = top;
+    wave_dense[wave] = dense;
+  }
+  __syncthreads();
+  const int32_t points = scan(wave_points[lane & 15], 16);
+  const int32_t total = __shfl(points, 15), lasts = wave_last[lane & 15];
+  at += (wave > 0 ? __shfl(points, wave - 1) : 0) - sum;
+  {
+    const unsigned long long m = __ballot(lane < wave && lasts > 0);
+    const int32_t earlier = __shfl(lasts, m ? 63 - __clzll(m) : 0);
+    if (!lower) prev = m ? earlier : 0;
+  }
+  float d = wave_dense[lane & 15];
+  for (int o = 8; o > 0; o >>= 1) d += __shfl_xor(d, o);
+  // the column around a point holds d / total of the counted ones, n / (2 l) for a
+  // sphere of l columns radius
+  const float all = float(n) * float(total) / float(samples);
+  if (threadIdx.x == 0 && word0 == 0 && total > 0) {
+    const float l = 0.5f * float(total) * float(total) / fmaxf(d, 1.0f);
+    atomicMin(&L.slots[slot_of(k)].rows, __float_as_uint(row_widths(l, all)));
+  }
+  const int32_t runs = d * float(n) <= kTwoRunsColumn * float(total) * float(samples) ? 2 * slabs : slabs;
+  // the strips that begin a run: another share at their middle than at the middle
+  // of the strip before
+  const float scale = 0.5f * float(runs) / float(total);
+  uint32_t begin = 0;
+#pragma unroll
+  for (int e = 0; e < kOwn; ++e) {
+    const bool differs = int32_t(float(2 * at + own[e]) * scale) != int32_t(float(2 * at - prev) * scale);
+    if (own[e] > 0 && prev > 0 && differs) begin |= 1u << e;
+    prev = own[e] > 0 ? own[e] : prev;
+    at += own[e];
+  }
+  const int32_t begins = __popc(begin);
+  int32_t number = scan(begins, 64);
+  if (lane == 63) wave_begins[wave] = number;
+  __syncthreads();
+  const int32_t numbers = scan(wave_begins[lane & 15], 16);
+  number += (wave > 0 ? __shfl(numbers, wave - 1) : 0) - begins;
+  uint64_t eight = 0;
+#pragma unroll
+  for (int e = 0; e < kOwn; ++e) {
+    if ((begin >> e) & 1u) run_column[++number] = strip_column(kOwn * threadIdx.x + e);
+    eight |= uint64_t(uint32_t(number)) << (8 * e);
+  }
+  run_of[threadIdx.x] = eight;
+  __syncthreads();
+
+  const uint8_t* const run_of_strip = reinterpret_cast<const uint8_t*>(run_of);
+  for (int32_t word = word0 + int32_t(threadIdx.x); word < word1; word += kSetsBlock) {
+    float after[4];
+    word_points(word + kSetsBlock, after);
+    uint32_t out = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float c = floorf(mine[e] * g.inv_w);
+      const uint32_t run = run_of_strip[mine[e] < inf ? strip_of(c) : 0u];
+      const uint32_t set = run < uint32_t(slabs) ? run : run - uint32_t(slabs);
+      const uint32_t v = run_column[run] == c ? set | 0x80u : set;
+      out |= (mine[e] < inf ? v : 0xffu) << (8 * e);
+      mine[e] = after[e];
+    }
+    L.cls[k * L.words + word] = out;
+  }
 }
 
 // Points per table, hash heads, occupancy bits, pending walks and buffered
@@ -235,31 +386,27 @@ __device__ __forceinline__ int32_t rank_in(unsigned long long m) {
 }
 
 // Work item u: sample time u / slabs and column set u % slabs.  Columns of width
-// w > D + margins run over all x; blocks of 2^shift columns belong to the column
-// sets in turn, so that any smooth distribution of x spreads evenly without a
-// look at it.  A set's table holds its own points and, for the pairs across a
-// block's upper edge, those of the next block's first column.  Each pair is met
-// once: from its lower column, from its lower row within a column, once within
-// a cell.  A set whose points exceed the table (all points in a few columns,
-// say) takes the time's satellites in runs: a table per run, every own point of
-// the time tested against each.
+// w > D + margins run over all x; a set is one or two runs of them.  A set's table
+// holds its own points and, for the pairs across a run's upper edge, those of the
+// next run's first column.  Each pair is met once: from its lower column, from its lower row
+// within a column, once within a cell.  A set whose points exceed the table (all
+// points in a few columns, say) takes the time's satellites in runs: a table per
+// run, every own point of the time tested against each.
 //
-// Bound by VALU issue: the stream of class bytes (every set reads its time's:
-// five instructions a point, half of the whole at 100,000 satellites) and the
-// cells' lookups.  One workgroup per time with a bucket sort by x in LDS took 219
-// us at 9,341 x 1,000, this kernel 140; buckets of x in device memory 2.6 ms for
-// the sweep alone at 100,000 x 144, with 110 candidates per point, this kernel
-// 0.59 ms.
+// The work: the stream of class bytes (every set reads its time's, five
+// instructions for four points) and the cells' lookups.  One workgroup per time
+// with a bucket sort by x in LDS took 219 us at 9,341 x 1,000, this kernel 123;
+// buckets of x in device memory 2.6 ms for the sweep alone at 100,000 x 144, with
+// 110 candidates per point, this kernel 0.48 ms.
 //
-// kOne: one set holds every point (n <= kSlabPoints): no classes, no geometry
-// kernel, no overflow.
+// kOne: one set holds every point (n <= kSlabPoints): no classes, no overflow.
 template <class TR, bool kOne>
 __global__ void __launch_bounds__(kSlabBlock, 8)
     screen_slab_kernel(const TR* __restrict__ r, SlabLayout L, int32_t n, int64_t T, double D, double D2, int64_t cap,
                        int32_t slabs, int32_t* __restrict__ pairs, double* __restrict__ dist,
                        unsigned long long* __restrict__ count) {
   __shared__ float4 point[kSlabPoints];  // x, y, z and the chain's next entry
-  __shared__ int32_t owner[kSlabPoints];  // satellite; ~satellite for the next block's points
+  __shared__ int32_t owner[kSlabPoints];  // satellite; ~satellite for the next runs' points
   __shared__ int32_t head[kSlabHeads];
   __shared__ uint32_t bits[kSlabBits / 32];  // cells (by a finer hash) that hold a point
   __shared__ uint16_t walks[kSlabWalks];
@@ -281,9 +428,10 @@ __global__ void __launch_bounds__(kSlabBlock, 8)
     const float* const Y = L.y + k * int64_t(n);
     const float* const Z = L.z + k * int64_t(n);
 
-    const SlabCells g = kOne ? cells_of(L.cells[slot_of(k)].near, D) : L.cells[slot_of(k)];
-    const float near = g.near, reach = g.reach;
-    const float inv_w = 1.0f / reach, inv_h = inv_w / row_widths(g, n), inv_width = 1.0f / float(g.width);
+    const SlabSlot& slot = L.slots[slot_of(k)];
+    const Cells g = cells_of(slot, D);
+    const float near = g.near, near_z = g.near_z, reach = g.reach, inv_w = g.inv_w;
+    const float inv_h = inv_w / (kOne ? row_widths(__uint_as_float(slot.rxy) * inv_w + 1.0f, float(n)) : __uint_as_float(slot.rows));
     auto column = [&](float x) { return column_of(x, inv_w); };
     auto row = [&](float y) { return int32_t(floorf(y * inv_h)); };
     // a cell's hash: its upper 11 bits are the head, its upper 15 the occupancy bit
@@ -294,14 +442,6 @@ __global__ void __launch_bounds__(kSlabBlock, 8)
       return ((bits[h >> 5] >> (h & 31)) & 1u) != 0;
     };
     static_assert(kSlabHeads == 1 << 11 && kSlabBits == 1 << 15, "hash bits");
-    // 2: a column of the set's own; 1: the first column of the block after an own
-    // one; 0: neither
-    auto belongs = [&](int32_t c) {
-      const uint32_t b = block_of(c, g.left, inv_width), set = b % uint32_t(slabs);
-      if (set == uint32_t(slab)) return 2;
-      return set == uint32_t((slab + 1) % slabs) && int32_t(b) * g.width == c - g.left ? 1 : 0;
-    };
-
     // Table of the set's points among satellites [lo, hi), lo a multiple of four;
     // returns how many the class bytes name (past kSlabPoints none is stored).
     // The stream only notes which satellites belong; coordinates and chains are
@@ -324,13 +464,15 @@ __global__ void __launch_bounds__(kSlabBlock, 8)
           word[e] = w < w1 ? classes[w] : 0xffffffffu;
         }
         // bit 8 b + e: point b of word e belongs (a byte of seven bits plus 0x7f
-        // reaches bit 7 unless it is zero)
-        uint32_t flags = 0;
+        // reaches bit 7 unless it is zero); above: those of a next run's first
+        // column
+        uint32_t flags = 0, above = 0;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const uint32_t low = word[e] & 0x7f7f7f7fu;
           const uint32_t own = ~((low ^ own_class) + 0x7f7f7f7fu), next = ~((low ^ next_class) + 0x7f7f7f7fu) & word[e];
           flags |= ((own | next) & 0x80808080u) >> (7 - e);
+          above |= (next & 0x80808080u) >> (7 - e);
         }
         if (__ballot(flags != 0) == 0) continue;
         // places in the list: a prefix sum of the lanes' counts, bit by bit
@@ -349,27 +491,27 @@ __global__ void __launch_bounds__(kSlabBlock, 8)
         while (flags != 0) {
           const int f = __ffs(flags) - 1;
           flags &= flags - 1;
-          if (at < kSlabPoints) owner[at] = 4 * (w0 + (f & 7) * kSlabBlock + int32_t(threadIdx.x)) + (f >> 3);
+          const int32_t i = 4 * (w0 + (f & 7) * kSlabBlock + int32_t(threadIdx.x)) + (f >> 3);
+          if (at < kSlabPoints) owner[at] = (above >> f) & 1u ? ~i : i;
           ++at;
         }
       }
       __syncthreads();
       const int32_t all = kOne ? n : held, m = all < kSlabPoints ? all : kSlabPoints;
       for (int32_t q = threadIdx.x; q < m; q += kSlabBlock) {
-        const int32_t i = kOne ? q : owner[q];
-        const float x = i < hi ? X[i] : __builtin_inff();
-        const int32_t c = column(x);
-        const int mine = !(x < __builtin_inff()) ? 0 : kOne ? 2 : belongs(c);
-        if (mine == 0) {
-          owner[q] = ~i;  // not of the set after all: in no chain
+        const int32_t w = kOne ? q : owner[q], i = w < 0 ? ~w : w;
+        const float x = X[i];
+        if (kOne && !(x < __builtin_inff())) {
+          owner[q] = ~i;  // invalid: in no chain, and takes no walks
           continue;
         }
+        const int32_t c = column(x);
         const float y = Y[i], z = Z[i];
         const uint32_t h = cell_hash(c, row(y));
         atomicOr(&bits[h >> (32 - 10)], 1u << ((h >> (32 - 15)) & 31));
         const int32_t next = atomicExch(&head[h >> (32 - 11)], q);
         point[q] = make_float4(x, y, z, __int_as_float(next));
-        if (kOne || mine == 1) owner[q] = mine == 1 ? ~i : i;
+        if (kOne) owner[q] = i;
       }
       __syncthreads();
       return all;
@@ -383,7 +525,14 @@ __global__ void __launch_bounds__(kSlabBlock, 8)
         event_pair[e] = make_int2(a, b);
         event_dist[e] = d;
       } else {
-        const unsigned long long g = atomicAdd(count, 1ull);
+        // past the buffer: one addition for the lanes that report together
+        const unsigned long long m = __ballot(1);
+        const int32_t rank = rank_in(m);
+        unsigned long long g = 0;
+        if (rank == 0) g = atomicAdd(count, (unsigned long long)__popcll(m));
+        g = (uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(int32_t(g >> 32)))) << 32) |
+            uint32_t(__builtin_amdgcn_readfirstlane(int32_t(g)));
+        g += uint32_t(rank);
         if (int64_t(g) < cap) {
           pairs[3 * g] = a;
           pairs[3 * g + 1] = b;
@@ -398,7 +547,7 @@ __global__ void __launch_bounds__(kSlabBlock, 8)
     auto walk = [&](int32_t q, int32_t c, int32_t b, bool after, float x, float y, float z, int32_t i) {
       while (q >= 0) {
         const float4 o = point[q];
-        if (fabsf(o.x - x) <= near && fabsf(o.y - y) <= near && fabsf(o.z - z) <= near && column(o.x) == c &&
+        if (fabsf(o.x - x) <= near && fabsf(o.y - y) <= near && fabsf(o.z - z) <= near_z && column(o.x) == c &&
             row(o.y) == b) {
           const int32_t w = owner[q], j = w < 0 ? ~w : w;
           if (!after || j > i) {
@@ -480,9 +629,7 @@ __global__ void __launch_bounds__(kSlabBlock, 8)
           const uint32_t word = classes[w];
           for (uint32_t f = ~(((word & 0x7f7f7f7fu) ^ own_class) + 0x7f7f7f7fu) & 0x80808080u; f != 0; f &= f - 1) {
             const int32_t i = 4 * w + ((__ffs(f) - 1) >> 3);
-            const float x = i < n ? X[i] : __builtin_inff();
-            if (!(x < __builtin_inff()) || belongs(column(x)) != 2) continue;
-            const float y = Y[i], z = Z[i];
+            const float x = X[i], y = Y[i], z = Z[i];
             const int32_t c = column(x), b = row(y), above = row(y + reach);
             const int32_t side = above != b ? above : row(y - reach);
             for (int e = 0; e < 4; ++e) {
@@ -769,14 +916,17 @@ bool screen_global_fits(int64_t n, int64_t T) {
   return n <= 0x7fffffff && n * T <= int64_t(0x7fffffff) * 256 && T <= 0x7fffffff;
 }
 
-// Column sets per time: a table has room for 30% more than a set's even share,
-// and a further quarter per 100,000 satellites, since the sets then have few
-// columns (28 at 100,000 satellites and 10 km).  The fullest set of the test
-// constellation's, 2 to 10 km, holds 2,300 to 2,750 of 3,072 points from 20,000
-// to 200,000 satellites; one that overflows works in runs, at about twice the
-// time.
+// Column sets per time: about 2,050 points each, less for larger catalogues (a
+// sixth at 200,000 satellites, whose shares are sampled and whose columns hold
+// more).  A table of 3,072 then has room for half a strip at either end of a run
+// and the column above: the fullest set of shells at 10 km holds 1,890 to 2,450
+// points from 9,341 to 200,000 satellites and, at 100 km, about 3,000 of 100,000,
+// also with single satellites at 42,164, 120,000 or 4e6 km or one in twenty on the
+// geostationary ring (2,400 each overflowed there from 50,000 satellites on).  A set
+// that overflows (a column of its own with more than 3,072 points, say) works in
+// runs of satellites.
 static int32_t slab_count(int64_t n) {
-  return n <= kSlabPoints ? 1 : int32_t((n * 13 / 10 + n * n / 400000 + kSlabPoints - 1) / kSlabPoints);
+  return n <= kSlabPoints ? 1 : int32_t((n + n * n / 1000000 + 2047) / 2048);
 }
 
 template <class TR>
@@ -793,9 +943,12 @@ static hipError_t screen_slabs(const TR* r, const uint8_t* err, int64_t n, int64
     hipLaunchKernelGGL((screen_slab_kernel<TR, true>), grid, dim3(kSlabBlock), 0, s, r, L, int32_t(n), T, D, D * D,
                        cap, slabs, pairs, dist, count);
   } else {
-    hipLaunchKernelGGL(slab_geometry, dim3(1), dim3(64), 0, s, L, D, slabs);
-    hipLaunchKernelGGL(screen_class, dim3(unsigned(T * ((L.words + 255) / 256))), dim3(256), 0, s, L, int32_t(n), T,
-                       slabs);
+    // workgroups per time: as many as fill the chip once (two on a compute unit;
+    // each counts the time's points anew), with a class word per lane at least
+    const int64_t parts = std::max<int64_t>(1, std::min((L.words + kSetsBlock - 1) / kSetsBlock, 512 / T));
+    const int64_t part_words = (L.words + parts - 1) / parts;
+    hipLaunchKernelGGL(screen_sets, dim3(unsigned(T * parts)), dim3(kSetsBlock), 0, s, L, int32_t(n), T, D, slabs,
+                       int32_t(parts), int32_t(part_words));
     hipLaunchKernelGGL((screen_slab_kernel<TR, false>), grid, dim3(kSlabBlock), 0, s, r, L, int32_t(n), T, D, D * D,
                        cap, slabs, pairs, dist, count);
   }
