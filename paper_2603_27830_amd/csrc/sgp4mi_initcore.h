@@ -462,16 +462,16 @@ __device__ inline void init_deep(const double el[7], const double* rec, double k
   const double n = rec[kN0pp];
   const double e = el[1], inc = el[2];
   double si, ci, sw, cw, snd, cnd;
-  sincos_rr(inc, &si, &ci);
-  sincos_rr(el[4], &sw, &cw);
-  sincos_rr(el[3], &snd, &cnd);
+  sincos_any(inc, &si, &ci);
+  sincos_any(el[4], &sw, &cw);
+  sincos_any(el[3], &snd, &cnd);
   // The Moon's orbit at epoch: node on the ecliptic, its inclination and node
   // on the equator (spherical triangle with the obliquity), its perigee
   // argument measured from that equatorial node.
   const double sin_eps = 0.39785416, cos_eps = 0.91744867, sin_il = 0.089683511;
   const double node_l = 4.5236020 - 9.2422029e-4 * day;
   double sl, cl;
-  sincos_rr(node_l, &sl, &cl);
+  sincos_any(node_l, &sl, &cl);
   const double cib_m = 0.91375164 - 0.03568096 * cl;
   const double sib_m = sqrt(1.0 - cib_m * cib_m);
   const double sh_l = sin_il * sl / sib_m;
@@ -479,7 +479,7 @@ __device__ inline void init_deep(const double el[7], const double* rec, double k
   const double perigee_l = 5.8351514 + 0.0019443680 * day;
   const double g_m = perigee_l + atan2(sin_eps * sl / sib_m, ch_l * cl + cos_eps * sh_l * sl) - node_l;
   double sg_m, cg_m;
-  sincos_rr(g_m, &sg_m, &cg_m);
+  sincos_any(g_m, &sg_m, &cg_m);
   double sec_s[5], sec_m[5];
   // Sun: node at the equinox, inclination the obliquity, perigee at 281.22 deg
   deep_body(0.1945905, -0.98088458, cos_eps, sin_eps, cnd, snd, cw, sw, ci, si, e, n, kSun, d + kDPer0, sec_s);

@@ -69,6 +69,21 @@ def test_states_with_a_large_node():
     assert np.abs(np.hypot(jac[0, 3], jac[1, 3]) - np.hypot(r[0], r[1])).max() <= 1e-8
 
 
+@pytest.mark.parametrize("row", [3, 4])
+def test_deep_space_terms_with_large_angles(row):
+    """The lunar-solar rates and coefficients: those of the reduced angle, their
+    sums of a few dozen products to 1e-12 of the largest of each kind."""
+    el = synth.deep_elements(LARGE.size, 5)
+    n = LARGE.size
+    terms = []
+    for angles in ([reduced(x) for x in LARGE], LARGE):
+        el[row] = angles
+        rec, *_ = states(el, np.zeros(1))
+        terms.append(rec.consts.cpu().numpy().view(np.float64)[64 + 64 * n:].reshape(n, 64)[:, :31])
+    print(f"[gpu] angles: deep-space terms, row {row}", flush=True)
+    assert (np.abs(terms[1] - terms[0]) <= 1e-12 * np.abs(terms[0]).max(axis=0)).all()
+
+
 @pytest.mark.parametrize("row", [3, 4, 5])
 def test_deep_space_states_with_large_angles_are_bounded(row):
     el = synth.deep_elements(8 * LARGE.size, 4)
