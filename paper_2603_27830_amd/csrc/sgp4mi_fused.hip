@@ -18,15 +18,17 @@
 
 namespace sgp4mi {
 
-constexpr int kFusedTT = 16;
 // Satellites of a workgroup: one wavefront initialises while the others wait, and
 // several workgroups on a compute unit fill the gaps.  128 lanes up to kFusedNarrow
 // times of a workgroup, 256 beyond: 1M x 8 FP64 164 us with 128 and 182 with 256,
 // 300,000 x 2 mixed 17 and 20, but 300,007 x 19 mixed 57 and 51, 20,000 x 200 FP64
 // 103 and 88.  (128 satellites on 256 lanes 66 us where 64 on 128 took 65, 256 on
-// 256 72.)
+// 256 72.)  Grids of up to two workgroups per compute unit take 256 lanes from four
+// times on (their points then need one pass: 4,096 deep-space satellites x 32 FP64 39
+// -> 25 us, near-Earth ones the same 12).
 constexpr int kFusedSats = 64;
 constexpr int kFusedNarrow = 8;
+constexpr int32_t kFusedLdsNarrow = 20416;  // an eighth of a compute unit's LDS
 
 struct FusedArgs {
   int64_t n, T;
@@ -37,6 +39,7 @@ struct FusedArgs {
   double vkms;
   double ref_day;       // reference instant of the epoch row, days after JD 2415020.0
   int64_t per;          // times per workgroup
+  int32_t round;        // deep-space members that LDS holds
 };
 
 // The satellite's constants as the two-stage path reads them from its slot:
@@ -81,14 +84,14 @@ __device__ __forceinline__ Grav grav_of(const FusedArgs& a) {
 
 // Initialisation of satellite i into rec (kNRec doubles); returns the info word
 // and, with it, the elements and the epoch for a deep-space satellite's terms.
-__device__ __forceinline__ uint32_t init_sat(const FusedArgs& a, const Grav& g, int64_t i, double* rec, double* el,
-                                             double* epoch) {
+__device__ __forceinline__ uint32_t init_sat(const FusedArgs& a, int64_t i, double* rec, double* el, double* epoch,
+                                             bool near_only) {
 #pragma unroll
   for (int k = 0; k < 7; ++k) el[k] = a.elem[k * a.n + i];
   *epoch = a.elem[7 * a.n + i];
   uint32_t code;
   bool isimp, dsp;
-  init_record<double>(a.grav, el, rec, &code, &isimp, &dsp);
+  init_record<double>(a.grav, el, rec, &code, &isimp, &dsp, near_only);
   rec[kEpochMin] = 1440.0 * *epoch;
   return code | (isimp ? kInfoIsimp : 0u) | (dsp ? kInfoDeep : 0u);
 }
@@ -104,48 +107,31 @@ __device__ __forceinline__ void put_flags(const FusedArgs& a, int64_t i, uint32_
   a.user_flags[i] = f;
 }
 
-// A deep-space satellite's times [t0, t1), initialised anew and written point by
-// point: apart from the near-Earth lanes, whose registers it would otherwise
-// share (its terms hold more values than the constants of a near-Earth loop).
-template <class TS, class TP, bool kOff32>
-__device__ __forceinline__ void fused_deep(const FusedArgs& a, const Grav& g, int64_t i, int64_t t0, int64_t t1,
-                                           const Out<TP, kOff32>& out) {
-  double rec[kNRec], deep[kNDeep], el[7], epoch;
-  const uint32_t info = init_sat(a, g, i, rec, el, &epoch);
-  init_deep(el, rec, g.ke, a.ref_day + epoch, deep);
-  put_flags(a, i, info, deep[kDRes] != 0.0);
-  const SatC<TS, TP> c = sat_of<TS, TP>(rec, info, deep);
-  for (int64_t j = t0; j < t1; ++j) {
-    asm volatile("" ::: "memory");  // the deep-space terms stay in memory between points
-    PointState<TP> s;
-    const uint32_t code = deep_point<TS, TP>(c, g, a.t[j], s);
-    out.put(i * a.T + j, code, s);
-  }
-}
-
 // One time: each lane initialises and propagates its own satellite.  Bound by
-// VALU issue: 1M satellites FP64 43 -> 38 us with the reciprocals and roots of
-// init_record; four wavefronts per SIMD (128 registers) spill and take 42.
+// VALU issue: 1M satellites FP64 43 -> 33 us with the reciprocals and roots of
+// init_record; four wavefronts per SIMD (128 registers) spill and take 42.  Both
+// kinds of satellite share the initialisation (repeated for deep-space ones behind
+// the near-Earth ones, 100,000 with 2 % of them took 30 us, 20.5 so).
 template <class TS, class TP, bool kOff32>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3)))
     fused_one_kernel(FusedArgs a, Out<TP, kOff32> out) {
   const int64_t i = int64_t(blockIdx.x) * 64 + threadIdx.x;
   if (i >= a.n) return;
   const Grav g = grav_of(a);
-  bool deep;
-  {
-    double rec[kNRec], el[7], epoch;
-    const uint32_t info = init_sat(a, g, i, rec, el, &epoch);
-    deep = (info & kInfoDeep) != 0;
-    if (!deep) {
-      put_flags(a, i, info, false);
-      const SatC<TS, TP> c = sat_of<TS, TP>(rec, info, nullptr);
-      PointState<TP> s;
-      const uint32_t code = sgp4_point<TS, TP>(c, g, a.t[0], s);
-      out.put(i, code, s);
-    }
+  double rec[kNRec], el[7], epoch;
+  const uint32_t info = init_sat(a, i, rec, el, &epoch, false);
+  PointState<TP> s;
+  uint32_t code;
+  if (info & kInfoDeep) {
+    double deep[kNDeep];
+    init_deep(el, rec, g.ke, a.ref_day + epoch, deep, false);
+    put_flags(a, i, info, deep[kDRes] != 0.0);
+    code = deep_point<TS, TP>(sat_of<TS, TP>(rec, info, deep), g, a.t[0], s);
+  } else {
+    put_flags(a, i, info, false);
+    code = sgp4_point<TS, TP>(sat_of<TS, TP>(rec, info, nullptr), g, a.t[0], s);
   }
-  if (deep) fused_deep<TS, TP, kOff32>(a, g, i, 0, 1, out);
+  out.put(i, code, s);
 }
 
 // The constants of one satellite as the near-Earth terms of each precision read
@@ -210,26 +196,115 @@ SGP4MI_LDS_REC(double, double)
 SGP4MI_LDS_REC(float, float)
 #undef SGP4MI_LDS_REC
 
+// The kernel's arguments as a function of its own reads them: through the
+// segment they are passed in (as references they would go to the stack).
+template <class TP, bool kOff32>
+struct FusedCall {
+  FusedArgs a;  // first
+  Out<TP, kOff32> out;
+};
+typedef const __attribute__((address_space(4))) uint32_t* KernArgs;
+template <class T>
+__device__ __forceinline__ T kernel_arguments(KernArgs p) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);  // the same in every lane
+  const uint32_t lo = __builtin_amdgcn_readfirstlane(uint32_t(v)), hi = __builtin_amdgcn_readfirstlane(uint32_t(v >> 32));
+  p = reinterpret_cast<KernArgs>(uint64_t(hi) << 32 | lo);
+  static_assert(sizeof(T) % 4 == 0 && alignof(T) <= 8, "whole words at the segment's start");
+  uint32_t w[sizeof(T) / 4];
+#pragma unroll
+  for (size_t k = 0; k < sizeof(T) / 4; ++k) w[k] = p[k];
+  T t;
+  __builtin_memcpy(&t, w, sizeof t);
+  return t;
+}
+
+// A deep-space member's constants and terms, as all of its points read them.
+struct LdsDeep {
+  static constexpr int kFew = 5;
+  double d[kEpochMin + 1], few[kFew], deep[kNDeep];  // few: kI0, kC1, kBC4, kA0pp, kE0
+  uint32_t info;
+  int32_t sat;  // of the workgroup
+  __device__ __forceinline__ void put(const double* rec) {
+#pragma unroll
+    for (int k = 0; k <= kEpochMin; ++k) d[k] = rec[k];
+    few[0] = rec[kI0]; few[1] = rec[kC1]; few[2] = rec[kBC4]; few[3] = rec[kA0pp]; few[4] = rec[kE0];
+  }
+  // what deep_point reads
+  template <class TS, class TP>
+  __device__ __forceinline__ SatC<TS, TP> sat_c() const {
+    SatC<TS, TP> c;
+    c.M0 = TS(d[kM0]); c.Mdot = TS(d[kMdot]); c.argp0 = TS(d[kArgp0]); c.argpdot = TS(d[kArgpdot]);
+    c.node0 = TS(d[kNode0]); c.nodedot = TS(d[kNodedot]); c.nodecf = TS(d[kNodecf]); c.t2cof = TS(d[kT2cof]);
+    c.n0pp = TS(d[kN0pp]); c.epoch_min = d[kEpochMin];
+    c.i0 = TP(few[0]); c.C1 = TS(few[1]); c.bC4 = TS(few[2]); c.a0pp = TS(few[3]); c.e0 = TS(few[4]);
+    c.info = info;
+    c.deep = deep;
+    return c;
+  }
+};
+
+// A deep-space member's initialisation into LDS, and one of its points.  Functions
+// of their own, without loops around them: the near-Earth loop does not share its
+// registers with the terms (inlined, 300,007 x 19 mixed without a deep-space member
+// took 58 us, 50 so), and no loop carries the hundred or so constants of their
+// series in scalar registers (one function with both loops: 278 us instead of 153 at
+// 100,000 deep-space satellites x 32 FP64).
+typedef __attribute__((address_space(3))) LdsDeep* LDeep;
+static __device__ __attribute__((noinline)) void fused_deep_init(KernArgs args, int64_t i, int32_t sat, LDeep to) {
+  const FusedArgs a = kernel_arguments<FusedArgs>(args);
+  LdsDeep& d = *(LdsDeep*)to;
+  double rec[kNRec], el[7], epoch;
+  const uint32_t info = init_sat(a, i, rec, el, &epoch, false);
+  d.info = info;
+  d.sat = sat;
+  d.put(rec);
+  init_deep(el, rec, a.grav.ke, a.ref_day + epoch, d.deep, false);
+  put_flags(a, i, info, d.deep[kDRes] != 0.0);
+}
+template <class TS, class TP, bool kOff32>
+__device__ __attribute__((noinline)) void fused_deep_point(KernArgs args, int64_t p, double t, LDeep from) {
+  const FusedCall<TP, kOff32> call = kernel_arguments<FusedCall<TP, kOff32>>(args);
+  const LdsDeep& d = *(const LdsDeep*)from;
+  PointState<TP> s;
+  const uint32_t code = deep_point<TS, TP>(d.sat_c<TS, TP>(), grav_of(call.a), t, s);
+  call.out.put(p, code, s);
+}
+
 // kFusedSats satellites, times [y per, (y + 1) per) of the list.  Bound by VALU
 // issue.  One wavefront of sixteen initialising for 64 satellites, in runs of 16
 // times, took 204 us at 300,007 x 19 mixed, this 51; a lane per satellite walking
 // its times in registers, outputs regrouped through LDS by eight times, 107
 // (pieces of cache lines); 1M x 8 FP64 240 -> 164, 300,000 x 2 mixed 32 -> 17.
+// Deep-space members: every point a lane, as for the others.  100,000 of them x 32
+// FP64 153 us, where walking the times on the lane that met the satellite took 1,022
+// and sixteen wavefronts behind one initialising 273; 15 % of them among near-Earth
+// ones 98, 793 and 230.
 template <class TS, class TP, bool kOff32, int kBlock>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4)))
-    fused_kernel(FusedArgs a, Out<TP, kOff32> out) {
-  __shared__ __align__(16) LdsSat<TS, TP> sats[kFusedSats];
+    fused_kernel(FusedCall<TP, kOff32> call) {
+  const FusedArgs& a = call.a;
+  const Out<TP, kOff32>& out = call.out;
+  // the near-Earth members' constants, then rounds of deep-space members
+  extern __shared__ __align__(16) unsigned char lds[];
+  LdsSat<TS, TP>* const sats = reinterpret_cast<LdsSat<TS, TP>*>(lds);
+  __shared__ unsigned long long deep_lanes;
   const int64_t i0 = int64_t(blockIdx.x) * kFusedSats;
   const int32_t ns = int32_t(a.n - i0 < kFusedSats ? a.n - i0 : kFusedSats);
   const Grav g = grav_of(a);
-  bool deep = false;
-  if (int32_t(threadIdx.x) < ns) {
-    double rec[kNRec], el[7], epoch;
-    const uint32_t info = init_sat(a, g, i0 + threadIdx.x, rec, el, &epoch);
-    deep = (info & kInfoDeep) != 0;
-    if (!deep) put_flags(a, i0 + threadIdx.x, info, false);
-    sats[threadIdx.x].put(rec);
-    sats[threadIdx.x].info = info;
+  if (threadIdx.x < kFusedSats) {
+    bool deep = false;
+    if (int32_t(threadIdx.x) < ns) {
+      double rec[kNRec], el[7], epoch;
+      const uint32_t info = init_sat(a, i0 + threadIdx.x, rec, el, &epoch, true);
+      deep = (info & kInfoDeep) != 0;
+      if (!deep) {
+        put_flags(a, i0 + threadIdx.x, info, false);
+        sats[threadIdx.x].put(rec);
+      }
+      sats[threadIdx.x].info = info;
+    }
+    const unsigned long long m = __ballot(deep);
+    if (threadIdx.x == 0) deep_lanes = m;
   }
   __syncthreads();
   const int64_t t0 = int64_t(blockIdx.y) * a.per;
@@ -253,7 +328,26 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))
       ++s;
     }
   }
-  if (deep) fused_deep<TS, TP, kOff32>(a, g, i0 + threadIdx.x, t0, t0 + nt, out);
+  // Deep-space members, a round of as many as LDS holds at a time: the lanes that met
+  // them initialise one each, then all lanes take the round's points in output order.
+  const unsigned long long members = deep_lanes;
+  if (members == 0) return;
+  const KernArgs args = (KernArgs)__builtin_amdgcn_kernarg_segment_ptr();
+  const LDeep deeps = (LDeep)(LdsDeep*)lds;
+  const bool mine = threadIdx.x < kFusedSats && (members >> threadIdx.x & 1ull);
+  const int32_t rank = mine ? __popcll(members & ((1ull << threadIdx.x) - 1ull)) : -1;
+  const int32_t nd = __popcll(members);
+  for (int32_t d0 = 0; d0 < nd; d0 += a.round) {
+    const int32_t m = nd - d0 < a.round ? nd - d0 : a.round;
+    __syncthreads();  // the near-Earth constants, the last round's
+    if (rank >= d0 && rank < d0 + m)
+      fused_deep_init(args, i0 + threadIdx.x, threadIdx.x, deeps + (rank - d0));
+    __syncthreads();
+    for (int32_t q = threadIdx.x; q < m * nt; q += kBlock) {
+      const int32_t e = q / nt, jd = q - e * nt;
+      fused_deep_point<TS, TP, kOff32>(args, (i0 + deeps[e].sat) * a.T + t0 + jd, a.t[t0 + jd], deeps + e);
+    }
+  }
 }
 
 template <class TP>
@@ -270,10 +364,20 @@ static void fused_go(const FusedArgs& a, void* r, void* v, uint8_t* err, hipStre
     return;
   }
   const dim3 grid(unsigned((a.n + kFusedSats - 1) / kFusedSats), unsigned((a.T + a.per - 1) / a.per));
-  if (a.per <= kFusedNarrow)
-    hipLaunchKernelGGL((fused_kernel<TS, TP, kOff32, 128>), grid, dim3(128), 0, s, a, o);
+  // LDS for all members' deep-space terms where that leaves as many workgroups on
+  // a compute unit: four of 256 lanes (sixteen wavefronts, as many as their
+  // registers allow), or grids of up to four workgroups each; else an eighth of
+  // the unit's
+  const bool wide = a.per > kFusedNarrow || (a.per >= 4 && int64_t(grid.x) * grid.y <= 512);
+  FusedArgs b = a;
+  b.round = wide || int64_t(grid.x) * grid.y <= 1024 ? kFusedSats : kFusedLdsNarrow / int32_t(sizeof(LdsDeep));
+  const size_t lds = std::max(sizeof(LdsDeep) * size_t(b.round), sizeof(LdsSat<TS, TP>) * kFusedSats);
+  static_assert(sizeof(LdsDeep) * kFusedSats <= 40000 && sizeof(LdsSat<TS, TP>) * kFusedSats <= kFusedLdsNarrow,
+                "four and eight workgroups on a compute unit");
+  if (wide)
+    hipLaunchKernelGGL((fused_kernel<TS, TP, kOff32, 256>), grid, dim3(256), lds, s, FusedCall<TP, kOff32>{b, o});
   else
-    hipLaunchKernelGGL((fused_kernel<TS, TP, kOff32, 256>), grid, dim3(256), 0, s, a, o);
+    hipLaunchKernelGGL((fused_kernel<TS, TP, kOff32, 128>), grid, dim3(128), lds, s, FusedCall<TP, kOff32>{b, o});
 }
 
 template <class TS, class TP>
@@ -282,13 +386,13 @@ static void fused_t(const FusedArgs& a, void* r, void* v, uint8_t* err, hipStrea
   else fused_go<TS, TP, false>(a, r, v, err, s);
 }
 
-// Largest T and n of a fused launch, as the interface states them (the grid
-// itself is smaller: 64 lanes per 64 satellites in x, at most 4,096 groups of
-// times in y).
-int64_t fused_max_T() { return int64_t(65535) * kFusedTT; }
+// Largest T and n of a fused launch, as the interface states them: 65,535 runs of 16
+// times, and 2^32 lanes at 64 per satellite group and run time (the grid itself is
+// smaller: at most 512 groups of times in y).
+constexpr int64_t kFusedRun = 16;
+int64_t fused_max_T() { return 65535 * kFusedRun; }
 bool fused_fits(int64_t n, int64_t T) {
-  const uint64_t tt = uint64_t(T < kFusedTT ? T : kFusedTT);
-  return grid_fits(uint64_t((n + 63) / 64), 64 * (tt > 0 ? tt : 1));
+  return grid_fits(uint64_t((n + 63) / 64), 64 * uint64_t(std::max<int64_t>(1, std::min(T, kFusedRun))));
 }
 
 hipError_t launch_fused(int precision, const double g[5], double ref_day, int64_t n, const double* elem,

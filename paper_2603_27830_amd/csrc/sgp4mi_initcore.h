@@ -102,10 +102,11 @@ inline GravIn grav_in(const double g[5]) {
 // el: n0 (Kozai, rad/min), e0, i0, node0, argp0, M0, bstar.  Writes the
 // record entries (all but kEpochMin), the satellite code and the flags
 // (simplified drag; deep space: period of 225 min or more, which also takes
-// the simplified drag terms).
+// the simplified drag terms).  near_only: a deep-space satellite gets its flags
+// only.
 template <class S>
 __device__ __forceinline__ void init_record(const GravIn& g, const S el[7], S rec[kNRec], uint32_t* code_out,
-                                            bool* isimp_out, bool* deep_out) {
+                                            bool* isimp_out, bool* deep_out, bool near_only = false) {
   using ::fabs;
   const S& no_kozai = el[0];
   const S& ecco = el[1];
@@ -160,6 +161,10 @@ __device__ __forceinline__ void init_record(const GravIn& g, const S el[7], S re
   else if (!(value(nbar) > 0.0)) code = 2;
   else if (value(nbar) <= kTwoPi / 225.0) deep = true;  // a period of 225 minutes or more
   const bool isimp = deep || value(perigee_er) < g.p220;
+  *code_out = code;
+  *isimp_out = isimp;
+  *deep_out = deep;
+  if (near_only && deep) return;
 
   // Power-law drag coefficients.
   const S above = abar - sfour;
@@ -247,9 +252,6 @@ __device__ __forceinline__ void init_record(const GravIn& g, const S el[7], S re
   const double k2 = 0.5 * J2;
   rec[kSpA1] = (1.5 * k2) * con41; rec[kSpX1h] = (0.5 * k2) * x1mth2; rec[kSpX1k] = k2 * x1mth2;
   rec[kSpX7q] = (-0.25 * k2) * x7thm1; rec[kSpCN] = (1.5 * k2) * cos_i; rec[kSpCI] = (1.5 * k2) * cos_i * sin_i;
-  *code_out = code;
-  *isimp_out = isimp;
-  *deep_out = deep;
 }
 
 // ---------------------------------------------------------- deep space --
@@ -348,7 +350,8 @@ __device__ inline double gmst1982(double day) {
 // Per-satellite resonance terms.  rec: the satellite's record (mean motion,
 // inclination functions, secular rates); d: its deep-space slot with the
 // lunar-solar rates already written; M0, node0, argp0, e0 from el.
-__device__ inline void init_resonance(const double el[7], const double* rec, double ke, double day, double* d) {
+__device__ inline void init_resonance(const double el[7], const double* rec, double ke, double day, double* d,
+                                      bool fill) {
   const double n = rec[kN0pp], e = el[1];
   const int cls = (n < 0.0052359877 && n > 0.0034906585) ? 1 : (n >= 8.26e-3 && n <= 9.24e-3 && e >= 0.5) ? 2 : 0;
   const double gsto = gmst1982(day);
@@ -356,6 +359,7 @@ __device__ inline void init_resonance(const double el[7], const double* rec, dou
   d[kDGsto] = gsto;
   d[kDXlamo] = 0.0;
   d[kDXfact] = 0.0;
+  if (cls == 0 && !fill) return;
 #pragma unroll
   for (int m = 0; m < 20; ++m) d[kDRc0 + m] = 0.0;
   if (cls == 0) return;
@@ -445,7 +449,9 @@ __device__ inline void init_resonance(const double el[7], const double* rec, dou
     d[kDXfact] = rec[kMdot] + d[kDMDt] + 2.0 * (rec[kNodedot] + d[kDNodeDt] - kEarthRot) - n;
   }
   d[kDXlamo] = d[kDXlamo] - kTwoPi * floor(d[kDXlamo] * kInvTwoPi);
-  for (int m = 0; m < nt; ++m) {
+#pragma unroll
+  for (int m = 0; m < 10; ++m) {
+    if (m >= nt) continue;
     double sp, cp;
     sincos_rr(ph[m], &sp, &cp);
     const double c = n2 * cf[m];
@@ -457,8 +463,10 @@ __device__ inline void init_resonance(const double el[7], const double* rec, dou
 // el: epoch elements as for init_record; rec: the satellite's record (its
 // recovered mean motion, inclination functions and secular rates); ke: the
 // gravity's ke; day: days after JD 2415020.0.  Writes the kNDeep entries of a
-// deep-space slot.
-__device__ inline void init_deep(const double el[7], const double* rec, double ke, double day, double* d) {
+// deep-space slot; fill: also the resonance terms (zeros) of a satellite without
+// resonance, which nothing reads.
+__device__ inline void init_deep(const double el[7], const double* rec, double ke, double day, double* d,
+                                 bool fill = true) {
   const double n = rec[kN0pp];
   const double e = el[1], inc = el[2];
   double si, ci, sw, cw, snd, cnd;
@@ -498,7 +506,7 @@ __device__ inline void init_deep(const double el[7], const double* rec, double k
   const double mm = 4.7199672 + 0.22997150 * day - perigee_l;
   d[kDMb0] = ms - kTwoPi * floor(ms * kInvTwoPi);
   d[kDMb1] = mm - kTwoPi * floor(mm * kInvTwoPi);
-  init_resonance(el, rec, ke, day, d);
+  init_resonance(el, rec, ke, day, d, fill);
 }
 
 }  // namespace sgp4mi
