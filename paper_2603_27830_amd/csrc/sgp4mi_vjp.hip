@@ -2,15 +2,14 @@
 // differentiated elements (paper section 5: gradients of the state with
 // respect to the initial orbital elements, including B*).
 //
-// A workgroup of four wavefronts takes a group of 1 to 8 satellites, the grid's
-// size apart.  The group's points are cut into chunks of 64 points of one
-// satellite, dealt to the wavefronts in turn; a lane recomputes the forward
-// pass of its points (nothing from the forward launch is stored) and sweeps
-// the per-point steps in reverse by hand, accumulating the adjoints of the
-// per-satellite constants in double.  Kepler's equation is differentiated
-// through the implicit-function theorem at its root.  A wavefront sums its
-// lanes' adjoints per satellite in a fixed order, the group adds its
-// wavefronts' sums in index order (no atomics, so results repeat bit for bit),
+// A workgroup of four wavefronts takes a group of 1 to 8 satellites.  The group's
+// points are cut into chunks of 64 points of one satellite, dealt to the wavefronts
+// in turn; a lane recomputes the forward pass of its points (nothing from the
+// forward launch is stored) and sweeps the per-point steps in reverse by hand,
+// accumulating the adjoints of the per-satellite constants in double.  Kepler's
+// equation is differentiated through the implicit-function theorem at its root.  A
+// wavefront sums its lanes' adjoints per satellite in a fixed order, the group adds
+// its wavefronts' sums in index order (no atomics, so results repeat bit for bit),
 // and seven lanes per satellite push the sums through the initialisation by
 // forward-mode duals, one element each: g_m = sum_k cbar_k * d c_k / d theta_m.
 #include "sgp4mi_grad64.h"
@@ -47,19 +46,48 @@ template <class TP> constexpr int kJacBlocksPerCU = sizeof(TP) == 8 ? 2 : 3;
 // Jacobian, 9,341 x 500: groups of two 468 us, of four 498.  The rule looks at
 // n and the mean list length alone, so a dense grid given as lists is grouped
 // as the grid is.
-// A group's satellites lie the grid's size apart, so that neighbours with long lists
-// (a catalogue sorted by observations) come to different workgroups: 64 lists of
-// 20,000 points side by side among 9,341 satellites 1,557 us in eight workgroups,
-// 284 in sixty-four.
 static int group_size(int64_t n, int64_t points, int want) {
   const int64_t chunks = std::max<int64_t>(1, (points / n + 63) / 64);
   return int(std::max<int64_t>(1, std::min<int64_t>({kGroupMax, want / chunks, n / 1024})));
 }
 
-// Satellites sat0, sat0 + step, ... of a group: one fewer where the last would be
-// past the end (groups are taken from 1,024 satellites each, so no more).
-__device__ __forceinline__ int group_members(int64_t n, int group, int64_t sat0, int64_t step) {
-  return sat0 + (group - 1) * step < n ? group : group - 1;
+// The workgroup's satellites: first, first + step, ...  A dense grid takes neighbours
+// (their rows adjoin: Jacobian of 9,341 x 300 275 us, 287 when a group's lay apart).
+// Lists lie the number of groups apart, an odd number so that short ones start on
+// different wavefronts, and neighbours with long lists (a catalogue sorted by
+// observations) come to different workgroups: 64 lists of 20,000 points side by side
+// among 9,341 satellites VJP 1,557 us in eight workgroups, 229 so.
+struct Group {
+  int64_t first, step;
+  int members;
+};
+template <bool kRagged>
+__host__ __device__ __forceinline__ int64_t group_count(int64_t n, int group) {
+  const int64_t groups = (n + group - 1) / group;
+  return kRagged ? groups | 1 : groups;
+}
+template <bool kRagged>
+__device__ __forceinline__ Group group_of(int64_t n, int group) {
+  Group g;
+  if (kRagged) {
+    g.first = blockIdx.x;
+    g.step = gridDim.x;
+    // one fewer where the last would be past the end (groups hold several only
+    // from 1,024 groups on, so no more)
+    g.members = g.first + (group - 1) * g.step < n ? group : group - 1;
+  } else {
+    g.first = int64_t(blockIdx.x) * group;
+    g.step = 1;
+    g.members = int(n - g.first < group ? n - g.first : group);
+  }
+  return g;
+}
+// The chunk a wavefront starts at: chunks are dealt to the wavefronts in turn, from
+// one that depends on the satellite and its count alone, so that a grid and the
+// same grid as lists add in the same order; neighbours of equal counts then share
+// the wavefronts evenly.
+__device__ __forceinline__ int64_t first_chunk(int wave, int64_t i, int64_t chunks) {
+  return (uint32_t(wave) - uint32_t(i) * uint32_t(chunks)) & (kVjpWaves - 1);
 }
 
 // Sum of each of acc[0..K) over the wavefront's 64 lanes: lane l ends with the
@@ -405,8 +433,9 @@ __global__ void __launch_bounds__(kVjpBlock, kVjpBlocksPerCU<double>)
   // the lanes' sums of the satellite at hand, then the wavefronts' of the group
   __shared__ double sums[kVjpWaves][kNAdj64][64];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t sat0 = blockIdx.x, step = gridDim.x;
-  const int ns = group_members(n, group, sat0, step);
+  const Group gp = group_of<kRagged>(n, group);
+  const int64_t sat0 = gp.first, step = gp.step;
+  const int ns = gp.members;
   if (int(threadIdx.x) < ns) infos[threadIdx.x] = rv.slots[sat0 + threadIdx.x * step].info;
   for (int q = threadIdx.x; q < ns * kNRec; q += kVjpBlock)
     consts[q / kNRec][q % kNRec] = rv.slots[sat0 + q / kNRec * step].d[q % kNRec];
@@ -414,7 +443,6 @@ __global__ void __launch_bounds__(kVjpBlock, kVjpBlocksPerCU<double>)
   if (int(threadIdx.x) < ns) grad64_extras(consts[threadIdx.x], rv.hdr[kHJ3oJ2]);
   __syncthreads();
   const Grav g = load_grav(rv);
-  uint32_t dealt = 0;  // chunks of the satellites before this one
   double kept[kNAdj64 / 8];
 #pragma unroll
   for (int k = 0; k < kNAdj64 / 8; ++k) kept[k] = 0.0;
@@ -424,8 +452,7 @@ __global__ void __launch_bounds__(kVjpBlock, kVjpBlocksPerCU<double>)
     const uint32_t info = __builtin_amdgcn_readfirstlane(infos[s]);
     // a satellite without states or derivatives (codes at epoch, deep space) has no work
     const int64_t chunks = (info & (kInfoCodeMask | kInfoDeep)) ? 0 : (cnt + 63) / 64;
-    const int64_t c0 = (uint32_t(wave) - dealt) & (kVjpWaves - 1);
-    dealt += uint32_t(chunks);
+    const int64_t c0 = first_chunk(wave, sat0 + s * step, chunks);
     const Adj64Sums lane_sums{&sums[wave][0][lane]};
     lane_sums.clear();
     const double* tt = kRagged ? t + p0 : t;
@@ -1016,8 +1043,9 @@ __global__ void __launch_bounds__(kVjpBlock, kJacBlocksPerCU<double>)
   __shared__ double parked[kVjpWaves][kNParked64][64];
   __shared__ uint32_t infos[kGroupMax];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t sat0 = blockIdx.x, step = gridDim.x;
-  const int ns = group_members(n, group, sat0, step);
+  const Group gp = group_of<kRagged>(n, group);
+  const int64_t sat0 = gp.first, step = gp.step;
+  const int ns = gp.members;
   if (int(threadIdx.x) < ns) infos[threadIdx.x] = rv.slots[sat0 + threadIdx.x * step].info;
   for (int q = threadIdx.x; q < ns * kNRec; q += kVjpBlock)
     consts[q / kNRec][q % kNRec] = rv.slots[sat0 + q / kNRec * step].d[q % kNRec];
@@ -1040,14 +1068,12 @@ __global__ void __launch_bounds__(kVjpBlock, kJacBlocksPerCU<double>)
   __syncthreads();
   const Grav g = load_grav(rv);
   const double qnan = __builtin_nan("");
-  uint32_t dealt = 0;  // chunks of the satellites before this one
   for (int s = 0; s < ns; ++s) {
     int64_t p0, cnt;
     list_of<kRagged>(offsets, sat0 + s * step, T, P, &p0, &cnt);
     const uint32_t info = __builtin_amdgcn_readfirstlane(infos[s]);
     const bool bad = (info & (kInfoCodeMask | kInfoDeep)) != 0;
-    const int64_t c0 = (uint32_t(wave) - dealt) & (kVjpWaves - 1);
-    dealt += uint32_t((cnt + 63) / 64);
+    const int64_t c0 = first_chunk(wave, sat0 + s * step, (cnt + 63) / 64);
     const double* tt = kRagged ? t + p0 : t;
     for (int64_t j = c0 * 64 + lane; j < cnt; j += kVjpBlock) {
       typedef __attribute__((address_space(1))) double* GDouble;
@@ -1117,8 +1143,8 @@ template <bool kRagged>
 static hipError_t jacobian64_go(int64_t n, const double* elem, const RecordView& rv, const int64_t* offsets,
                                 const double* t, int64_t T, int64_t P, double* jac, hipStream_t s) {
   const int group = std::min(kJacGroupMax, group_size(n, P, 16));
-  hipLaunchKernelGGL(jacobian64_kernel<kRagged>, dim3(unsigned((n + group - 1) / group)), dim3(kVjpBlock), 0, s, rv, n,
-                     elem, offsets, t, T, P, jac, group);
+  hipLaunchKernelGGL(jacobian64_kernel<kRagged>, dim3(unsigned(group_count<kRagged>(n, group))), dim3(kVjpBlock), 0, s,
+                     rv, n, elem, offsets, t, T, P, jac, group);
   return hipGetLastError();
 }
 
@@ -1137,8 +1163,8 @@ static hipError_t vjp64_go(int64_t n, const double* elem, const RecordView& rv, 
                            const double* t, int64_t T, int64_t P, const void* gr, const void* gv, double* gelem,
                            hipStream_t s) {
   const int group = group_size(n, P, 32);
-  hipLaunchKernelGGL(vjp64_kernel<kRagged>, dim3(unsigned((n + group - 1) / group)), dim3(kVjpBlock), 0, s, rv, n,
-                     elem, offsets, t, T, P, static_cast<const double*>(gr), static_cast<const double*>(gv), gelem,
+  hipLaunchKernelGGL(vjp64_kernel<kRagged>, dim3(unsigned(group_count<kRagged>(n, group))), dim3(kVjpBlock), 0, s, rv,
+                     n, elem, offsets, t, T, P, static_cast<const double*>(gr), static_cast<const double*>(gv), gelem,
                      group);
   return hipGetLastError();
 }
