@@ -66,7 +66,7 @@ constexpr int64_t kFlatBelowT = 64;
 // kernel (initialisation kept on chip); longer ones, given a record
 // workspace, run initialisation and the default dense launch.
 constexpr int64_t kFusedMaxT = 32;
-// Workgroup size of the VJP and Jacobian kernels (one workgroup per satellite).
+// Workgroup size of the VJP and Jacobian kernels (at most one workgroup per satellite).
 constexpr uint64_t kVjpLanes = 256;
 // Default dense launch: one wavefront per 64-time tile with the satellite's
 // constants in scalar registers, in 256-wide workgroups for FP64 and 512-wide
@@ -597,7 +597,7 @@ int sgp4_vjp(int64_t n, const double* elem, const void* consts, const double* t,
              const void* gr, const void* gv, double* gelem, void* stream) {
   if (n < 0 || T < 0 || n > kMaxSats || mul_overflows(n, T) || mul_overflows(n * T, 3)) return SGP4_E_SIZE;
   if (precision != SGP4_FP64 && precision != SGP4_FP32_MIXED) return SGP4_E_PRECISION;
-  if (!grid_fits(uint64_t(n), kVjpLanes)) return SGP4_E_SIZE;  // one workgroup per satellite
+  if (!grid_fits(uint64_t(n), kVjpLanes)) return SGP4_E_SIZE;  // at most one workgroup per satellite
   if (n == 0) return SGP4_OK;
   if (!elem || !consts || !gelem || (T > 0 && (!t || !gr))) return SGP4_E_ARG;
   return hip_status(launch_vjp(precision, n, elem, consts, t, T, gr, gv, gelem, static_cast<hipStream_t>(stream)));
@@ -607,7 +607,7 @@ int sgp4_vjp_ragged(int64_t n, const double* elem, const void* consts, const int
                     int64_t nnz, int precision, const void* gr, const void* gv, double* gelem, void* stream) {
   if (n < 0 || nnz < 0 || n > kMaxSats || mul_overflows(nnz, 3)) return SGP4_E_SIZE;
   if (precision != SGP4_FP64 && precision != SGP4_FP32_MIXED) return SGP4_E_PRECISION;
-  if (!grid_fits(uint64_t(n), kVjpLanes)) return SGP4_E_SIZE;  // one workgroup per satellite
+  if (!grid_fits(uint64_t(n), kVjpLanes)) return SGP4_E_SIZE;  // at most one workgroup per satellite
   if (n == 0) return SGP4_OK;
   if (!elem || !consts || !offsets || !gelem || (nnz > 0 && (!t || !gr))) return SGP4_E_ARG;
   return hip_status(launch_vjp_ragged(precision, n, elem, consts, offsets, t, nnz, gr, gv, gelem,
@@ -618,7 +618,7 @@ int sgp4_jacobian(int64_t n, const double* elem, const void* consts, const doubl
                   double* jac, void* stream) {
   if (n < 0 || T < 0 || n > kMaxSats || mul_overflows(n, T) || mul_overflows(n * T, 42)) return SGP4_E_SIZE;
   if (precision != SGP4_FP64 && precision != SGP4_FP32_MIXED) return SGP4_E_PRECISION;
-  if (!grid_fits(uint64_t(n), kVjpLanes)) return SGP4_E_SIZE;  // one workgroup per satellite
+  if (!grid_fits(uint64_t(n), kVjpLanes)) return SGP4_E_SIZE;  // at most one workgroup per satellite
   if (n == 0 || T == 0) return SGP4_OK;
   if (!elem || !consts || !t || !jac) return SGP4_E_ARG;
   return hip_status(launch_jacobian(precision, n, elem, consts, t, T, jac, static_cast<hipStream_t>(stream)));
@@ -628,7 +628,7 @@ int sgp4_jacobian_ragged(int64_t n, const double* elem, const void* consts, cons
                          int64_t nnz, int precision, double* jac, void* stream) {
   if (n < 0 || nnz < 0 || n > kMaxSats || mul_overflows(nnz, 42)) return SGP4_E_SIZE;
   if (precision != SGP4_FP64 && precision != SGP4_FP32_MIXED) return SGP4_E_PRECISION;
-  if (!grid_fits(uint64_t(n), kVjpLanes)) return SGP4_E_SIZE;  // one workgroup per satellite
+  if (!grid_fits(uint64_t(n), kVjpLanes)) return SGP4_E_SIZE;  // at most one workgroup per satellite
   if (n == 0 || nnz == 0) return SGP4_OK;
   if (!elem || !consts || !offsets || !t || !jac) return SGP4_E_ARG;
   return hip_status(launch_jacobian_ragged(precision, n, elem, consts, offsets, t, nnz, jac,

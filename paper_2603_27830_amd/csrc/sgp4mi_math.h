@@ -24,22 +24,13 @@ constexpr double kRotMax = 0.05;
 // Double-precision constants live in constant memory: gfx9 VALU instructions
 // take no 64-bit literals, and scalar-register operands (one per instruction)
 // avoid holding every coefficient in a vector register pair.
-// The small-angle rotation reads its terms from indices 7-9 and 16-18; the
-// other orders are kept for reference.
-__constant__ double kHalfAngle64[24] = {
-    // sin h = h + h^3 * P(h^2): -1/3!, 1/5!, ..., 1/21! (index 0 = highest order)
-    1.95729410633912612308e-20, -8.22063524662432971696e-18, 2.8114572543455207632e-15,
-    -7.6471637318198164759e-13, 1.60590438368216145994e-10, -2.50521083854417187751e-8,
-    2.75573192239858906526e-6, -1.98412698412698412698e-4, 8.33333333333333333333e-3,
-    -1.66666666666666666667e-1,
-    // cos h = 1 + h^2 * Q(h^2): -1/2!, 1/4!, ..., 1/20! (index 10 = highest order)
-    4.11031762331216485848e-19, -1.56192069685862264622e-16, 4.77947733238738529744e-14,
-    -1.14707455977297247139e-11, 2.08767569878680989792e-9, -2.75573192239858906526e-7,
-    2.48015873015873015873e-5, -1.38888888888888888889e-3, 4.16666666666666666667e-2, -0.5,
-    // 1 / (2*pi), 2*pi (double nearest), 2*pi minus that
-    0.15915494309189533577, 6.2831853071795864769, 2.4492935982947063e-16,
-    // unused
-    0.0};
+__constant__ double kSmall64[7] = {
+    // sin d = d + d^3 (-1/3! + d^2 (1/5! - d^2 / 7!)), highest order first
+    -1.98412698412698412698e-4, 8.33333333333333333333e-3, -1.66666666666666666667e-1,
+    // cos d = 1 + d^2 (-1/2 + d^2 (1/4! + d^2 (-1/6! + d^2 / 8!)))
+    2.48015873015873015873e-5, -1.38888888888888888889e-3, 4.16666666666666666667e-2,
+    // 1 / (2 pi)
+    0.15915494309189533577};
 
 __device__ __forceinline__ void half_angle(float h, float* s, float* c) {
   const float h2 = h * h;
@@ -218,7 +209,7 @@ __device__ __forceinline__ void sincos_hw(double x, float* s, float* c) {
   *c = __builtin_amdgcn_cosf(r);
 }
 __device__ __forceinline__ void sincos_hw_mem(double x, float* s, float* c) {
-  const float r = float(__builtin_amdgcn_fract(x * kHalfAngle64[20]));
+  const float r = float(__builtin_amdgcn_fract(x * kSmall64[6]));
   *s = __builtin_amdgcn_sinf(r);
   *c = __builtin_amdgcn_cosf(r);
 }
@@ -229,13 +220,13 @@ __device__ __forceinline__ void sincos_hw(float x, float* s, float* c) {
 }
 
 __device__ __forceinline__ void small_sc(double d, double* sd, double* cd) {
-  const double* k = kHalfAngle64;
+  const double* k = kSmall64;
   const double d2 = d * d;
-  double ps = fma(d2, k[7], k[8]);  // -1/7!, 1/5!
-  ps = fma(ps, d2, k[9]);            // -1/3!
+  double ps = fma(d2, k[0], k[1]);
+  ps = fma(ps, d2, k[2]);
   *sd = fma(ps * d2, d, d);
-  double pc = fma(d2, k[16], k[17]);  // 1/8!, -1/6!
-  pc = fma(pc, d2, k[18]);            // 1/4!
+  double pc = fma(d2, k[3], k[4]);
+  pc = fma(pc, d2, k[5]);
   pc = fma(pc, d2, -0.5);
   *cd = fma(pc, d2, 1.0);
 }
@@ -295,8 +286,9 @@ __device__ __forceinline__ void rotate_tiny(float* s, float* c, float d) {
 // 1 + e / 2 + 3 e^2 / 8 (an ulp or so; the root for positive arguments); in
 // float the hardware estimate alone (about 1 ulp).  rcp_from refines an estimate
 // that the caller has (relative error below 1e-5).  x^(-2/3), the semi-major axis
-// of a mean motion: a float estimate of x^(-1/3) (relative error below 2^-21)
-// and one third-order step; arguments beyond float's comfortable range take the
+// of a mean motion: a float estimate of x^(-1/3) (relative error below 2^-19 from
+// 1e-30 to 1e30: half an ulp of the exponent, up to 33, in the power) and one
+// third-order step; arguments beyond float's comfortable range take the
 // library's cube root.
 __device__ __forceinline__ double rcp_from(double x, double y) {
   const double e = fma(-x, y, 1.0);

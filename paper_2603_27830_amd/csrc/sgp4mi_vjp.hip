@@ -30,10 +30,9 @@ constexpr int kVjpWaves = kVjpBlock / 64;
 // Satellites per group at most: 7 x 8 lanes of one wavefront run the VJP's
 // duals; the Jacobian keeps 2,240 bytes of sensitivities per satellite.
 constexpr int kGroupMax = 8, kJacGroupMax = 4;
-// Workgroups per compute unit the register allocation must allow (one
-// wavefront per SIMD each).
-template <class TP> constexpr int kVjpBlocksPerCU = 3;
-template <class TP> constexpr int kJacBlocksPerCU = sizeof(TP) == 8 ? 2 : 3;
+// Workgroups per compute unit the register allocation must allow (one wavefront
+// per SIMD each).
+constexpr int kVjpBlocksPerCU = 3, kJacMixedBlocksPerCU = 3, kJac64BlocksPerCU = 2;
 
 // Satellites per group, so that a group has about `want` 64-point chunks.  The
 // duals of the initialisation (a serial chain of ~1,000 instructions on seven
@@ -146,8 +145,7 @@ __device__ __forceinline__ uint32_t point_vjp(const SatC<TS, TP>& c, const Grav&
     sM = sMdf;
     cM = cMdf;
     // As the forward kernel: float paths take the hardware sine and cosine of M.
-    if (sizeof(TP) == 4 || vabs(dMa) > TS(kRotMax)) TR::sc_damped(M, &sM, &cM);
-    else rotate_small(&sM, &cM, TP(dMa));
+    TR::sc_damped(M, &sM, &cM);
     Ed = Ed + c.bC5 * TS(sM - c.sinM0);
     Ld = Ld + c.t3cof * t3 + t4 * (c.t4cof + t * c.t5cof);
   }
@@ -423,7 +421,7 @@ __device__ __forceinline__ void list_of(const int64_t* __restrict__ offsets, int
 // open.  9,341 x 1,000 with both cotangents 523 -> 347 us; 9,341 lists of 79
 // points on average 316 -> 85 us (one 256-lane workgroup per list before).
 template <bool kRagged>
-__global__ void __launch_bounds__(kVjpBlock, kVjpBlocksPerCU<double>)
+__global__ void __launch_bounds__(kVjpBlock, kVjpBlocksPerCU)
     vjp64_kernel(RecordView rv, int64_t n, const double* __restrict__ elem, const int64_t* __restrict__ offsets,
                  const double* __restrict__ t, int64_t T, int64_t P, const double* __restrict__ gr,
                  const double* __restrict__ gv, double* __restrict__ gelem, int group) {
@@ -591,7 +589,7 @@ __device__ __forceinline__ void vjp_sat(const RecordView& rv, int64_t n, const d
 }
 
 template <class TS, class TP>
-__global__ void __launch_bounds__(kVjpBlock, kVjpBlocksPerCU<TP>)
+__global__ void __launch_bounds__(kVjpBlock, kVjpBlocksPerCU)
     vjp_kernel(RecordView rv, int64_t n, const double* __restrict__ elem, const double* __restrict__ t, int64_t T,
                const TP* __restrict__ gr, const TP* __restrict__ gv, double* __restrict__ gelem) {
   const int64_t i = blockIdx.x;
@@ -602,7 +600,7 @@ __global__ void __launch_bounds__(kVjpBlock, kVjpBlocksPerCU<TP>)
 // workgroup clamps its two offsets to [0, nnz] (and the end to at least the
 // start), so malformed offsets never read outside t, gr or gv.
 template <class TS, class TP>
-__global__ void __launch_bounds__(kVjpBlock, kVjpBlocksPerCU<TP>)
+__global__ void __launch_bounds__(kVjpBlock, kVjpBlocksPerCU)
     vjp_ragged_kernel(RecordView rv, int64_t n, const double* __restrict__ elem, const int64_t* __restrict__ offsets,
                       const double* __restrict__ t, int64_t nnz, const TP* __restrict__ gr,
                       const TP* __restrict__ gv, double* __restrict__ gelem) {
@@ -623,8 +621,8 @@ __global__ void __launch_bounds__(kVjpBlock, kVjpBlocksPerCU<TP>)
 // contracted with the elements' tangents.  Mixed: jacobian_kernel, forward mode
 // carried through every step, whose float rounding its results keep.
 //
-// Forward mode: one workgroup per satellite; seven lanes first push the unit
-// tangents of the elements through the initialisation (forward-mode duals)
+// Forward mode (mixed): one workgroup per satellite; seven lanes first push the
+// unit tangents of the elements through the initialisation (forward-mode duals)
 // into the constants' sensitivities dc[m][k] = dc_k / dtheta_m (LDS).  Then
 // every lane carries the seven tangents of each intermediate of its point
 // through one pass of the forward kernel's formulation, beside the values:
@@ -742,8 +740,7 @@ __device__ __forceinline__ uint32_t point_jvp(const SatC<TS, TP>& c, const Grav&
     tacc(A_t, -t3, ctan<TS, D>(dc, kD3));
     tacc(A_t, -t4, ctan<TS, D>(dc, kD4));
     TP sM = sMdf, cM = cMdf;
-    if (sizeof(TP) == 4 || vabs(dMa) > TS(kRotMax)) TR::sc_damped(M, &sM, &cM);
-    else rotate_small(&sM, &cM, TP(dMa));
+    TR::sc_damped(M, &sM, &cM);
     // Ed += bC5 (sin M - sinM0)
     const TS dsM = TS(sM - c.sinM0);
     Ed = Ed + c.bC5 * dsM;
@@ -1035,7 +1032,7 @@ __device__ __forceinline__ void jac_sat(const RecordView& rv, int64_t n, const d
 // of the launch, the 1.57 GB of stores need about 240 us; two wavefronts per
 // SIMD (the columns hold 72 registers) leave latencies open in between.
 template <bool kRagged>
-__global__ void __launch_bounds__(kVjpBlock, kJacBlocksPerCU<double>)
+__global__ void __launch_bounds__(kVjpBlock, kJac64BlocksPerCU)
     jacobian64_kernel(RecordView rv, int64_t n, const double* __restrict__ elem, const int64_t* __restrict__ offsets,
                       const double* __restrict__ t, int64_t T, int64_t P, double* __restrict__ jac, int group) {
   __shared__ double consts[kJacGroupMax][kNGrad64];
@@ -1119,7 +1116,7 @@ __global__ void __launch_bounds__(kVjpBlock, kJacBlocksPerCU<double>)
 }
 
 template <class TS, class TP>
-__global__ void __launch_bounds__(kVjpBlock, kJacBlocksPerCU<TP>)
+__global__ void __launch_bounds__(kVjpBlock, kJacMixedBlocksPerCU)
     jacobian_kernel(RecordView rv, int64_t n, const double* __restrict__ elem, const double* __restrict__ t,
                     int64_t T, double* __restrict__ jac) {
   const int64_t i = blockIdx.x;
@@ -1128,7 +1125,7 @@ __global__ void __launch_bounds__(kVjpBlock, kJacBlocksPerCU<TP>)
 
 // CSR time lists, offsets clamped per workgroup as for the ragged VJP.
 template <class TS, class TP>
-__global__ void __launch_bounds__(kVjpBlock, kJacBlocksPerCU<TP>)
+__global__ void __launch_bounds__(kVjpBlock, kJacMixedBlocksPerCU)
     jacobian_ragged_kernel(RecordView rv, int64_t n, const double* __restrict__ elem,
                            const int64_t* __restrict__ offsets, const double* __restrict__ t, int64_t nnz,
                            double* __restrict__ jac) {
