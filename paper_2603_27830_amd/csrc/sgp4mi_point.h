@@ -327,11 +327,12 @@ __device__ __forceinline__ void rotate_node64(double* su, double* cu, double du,
 // Rotations fall back to a full evaluation when the angle exceeds kRotMax.
 // In double every quotient is a product of 1 / sqrt(a), 1 / sqrt(1 - eL^2),
 // 1 / (1 - ecE), 1 / (1 + betal) and 1 / (1 - e^2).  FP64 is bound by vector
-// instructions (95 % of the cycles at 100,000 satellites x 1008 times): with
+// instructions (92 % of the cycles at 100,000 satellites x 1008 times): with
 // those, the folded short-period coefficients, the one-step Kepler solution, the
 // shorter rotations, the table index without a conversion and the series in eL^2
-// a point of 9,341 x 1,000 takes 323 of them instead of 435, and 100,000 x 1008
-// 1,317 us instead of 1,667.  In float the one-step solution, the series and the
+// a point of 9,341 x 1,000 takes 330 of them instead of 435 (seven are the check
+// that the angles are within the sine table's reach), and 100,000 x 1008 1,411 us
+// instead of 1,713.  In float the one-step solution, the series and the
 // shorter rotations leave 203 of 225: 9,341 x 1,000 mixed 66.0 -> 62.7 us with its
 // initialisation.
 template <class TS, class TP>

@@ -13,16 +13,19 @@
 // y and z of every valid point time-major into the workspace (64 x 64 tiles
 // through LDS, so that both the reads along times and the writes along
 // satellites are coalesced; invalid points get x = +inf), and the largest
-// coordinate of each tile.  Then workgroups of 1,024 lanes each take one sample
-// time and one set of x columns of it: they stream the time's x values, collect
-// the points of their columns in LDS in a hash table of (x, y) cells, and test
-// each point against the cells that can hold a partner.  The other (mode 2, and
-// catalogues beyond kSlabMaxN) sorts buckets of x in device memory.
+// |x| or |y| and the largest |z| of each slot of times.  A second pass counts
+// each time's points by strips of x, deals the strips out as sets of equally many
+// points, and writes a class byte per point that names its set.  Then workgroups
+// of 1,024 lanes each take one sample time and one set of it: they stream the
+// time's class bytes, collect the points of their set in LDS in a hash table of
+// (x, y) cells, and test each point against the cells that can hold a partner.
+// The other path (mode 2, and catalogues beyond kSlabMaxN) sorts buckets of x in
+// device memory.
 //
 // A candidate is taken to the exact test, on the stored positions, when its
 // float coordinates are within D plus a rounding margin in every axis.  The
-// margin, 2.4e-7 R for coordinates up to R, covers the two roundings (2^-24
-// relative each), so no pair closer than D is pruned.
+// margin, 2.4e-7 R for coordinates up to R (one R for x and y, one for z), covers
+// the two roundings (2^-24 relative each), so no pair closer than D is pruned.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

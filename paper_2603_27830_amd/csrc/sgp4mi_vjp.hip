@@ -416,10 +416,11 @@ __device__ __forceinline__ void list_of(const int64_t* __restrict__ offsets, int
 // Dense: times t[0..T) of every satellite, P = n T; CSR: satellite i's points
 // offsets[i] .. offsets[i+1]-1 at times t[p], P = nnz.  Cotangent rows of P.
 //
-// Bound by VALU issue (FP64, about 710 instructions per 64 points, 61% of the
-// launch's cycles) and by the latencies that three wavefronts per SIMD leave
-// open.  9,341 x 1,000 with both cotangents 523 -> 347 us; 9,341 lists of 79
-// points on average 316 -> 85 us (one 256-lane workgroup per list before).
+// Bound by VALU issue (FP64, about 650 instructions per 64 points with the
+// group's initialisation, 51% of the launch's cycles) and by the latencies that
+// three wavefronts per SIMD leave open.  9,341 x 1,000 with both cotangents 523 ->
+// 330 us; 9,341 lists of 79 points on average 316 -> 85 us (one 256-lane workgroup
+// per list before).
 template <bool kRagged>
 __global__ void __launch_bounds__(kVjpBlock, kVjpBlocksPerCU)
     vjp64_kernel(RecordView rv, int64_t n, const double* __restrict__ elem, const int64_t* __restrict__ offsets,
@@ -1028,7 +1029,7 @@ __device__ __forceinline__ void jac_sat(const RecordView& rv, int64_t n, const d
 // duals run before the points, since the points need the sensitivities).  The
 // stores are ordinary ones: rows of T doubles start inside cache lines, and the
 // L2 merges the pieces (non-temporal 468 us, ordinary 404 at 9,341 x 500).
-// 9,341 x 500: 566 -> 410 us; 9,341 x 30: 138 -> 59 us.  VALU issue takes 46%
+// 9,341 x 500: 566 -> 410 us; 9,341 x 30: 138 -> 59 us.  VALU issue takes 42%
 // of the launch, the 1.57 GB of stores need about 240 us; two wavefronts per
 // SIMD (the columns hold 72 registers) leave latencies open in between.
 template <bool kRagged>
